@@ -90,43 +90,124 @@ __device__ bool kp_draw(double a, int site, int mu, int k, long long n, uint32_t
     return false;
 }
 
-__device__ __forceinline__ int hop(const int *L, const int c[4], int s, int mu, int step, const int *stride)
+// The generator works on a copy of the links in the workspace, split by site
+// parity so that the sites of one class are consecutive: [4][9][V], the sites
+// of parity p (of x + y + z + t) in the half p of every plane, in
+// lexicographic order, x halved. The copy takes the two two-row link buffers
+// (768 bytes per site for 576 needed), which hold nothing between calls.
+__device__ __forceinline__ double2 *hb_links(const Cfg &C) { return C.U12[0]; }
+
+// Element s of the copy: site of parity par, (xh, row) = (x / 2, y + Ly (z + Lz t)).
+struct HbGeom {
+    int half, V2h, V3h;  // Lx / 2 sites of a parity per row; per xy-plane; per (x, y, z) volume
+};
+
+// A link of the copy. FULL: all nine elements, the caller's matrices (a
+// call's first sweep). Otherwise two rows, the third rebuilt: every link is
+// then one that m3_reunit has projected, whose third row is m3_row2 of the
+// other two, so both forms give the same matrix bit for bit. The element
+// offset within a plane is an unsigned 32-bit byte count (16 V < 2^32 for
+// every V the library takes), so the plane's address stays in scalar
+// registers.
+template <bool FULL>
+__device__ __forceinline__ M3 hb_load(const double2 *base, int V, int s)
 {
-    const int x = c[mu] + step;
-    if (x < 0) return s + (L[mu] - 1) * stride[mu];
-    if (x >= L[mu]) return s - (L[mu] - 1) * stride[mu];
-    return s + step * stride[mu];
+    M3 m;
+    const uint32_t off = (uint32_t)s * 16u;
+#pragma unroll
+    for (int k = 0; k < (FULL ? 9 : 6); ++k)
+        m.e[k] = *(const double2 *)((const char *)(base + (size_t)k * V) + off);
+    return m;
 }
 
-// Staple sum A of U_mu(s): U_mu(s) A is the sum of the six plaquettes through
-// it (upper U_nu(s+mu) U_mu^dag(s+nu) U_nu^dag(s), lower U_nu^dag(s+mu-nu)
-// U_mu^dag(s-nu) U_nu(s-nu), nu ascending).
-__device__ M3 staple_sum(const Cfg &C, int s, const int c[4], int mu)
+// Orders the staples: what is loaded after the fence is issued after this
+// sum is formed. Without it the compiler issues the loads of all six staples
+// first (430 registers' worth), which spills.
+__device__ __forceinline__ void hb_fence(M3 &A)
 {
-    const int V = C.V;
-    const int stride[4] = {1, C.dims[0], C.V2, C.V3};
-    const double2 *__restrict__ U = C.U;
-    M3 A = m3_zero();
-    int cp[4] = {c[0], c[1], c[2], c[3]};
-    cp[mu] = (c[mu] + 1 == C.dims[mu]) ? 0 : c[mu] + 1;
-    const int sp = hop(C.dims, c, s, mu, +1, stride);
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu) continue;
-        {
-            const M3 a = m3_load(U + (size_t)nu * 9 * V, V, sp);
-            const M3 b = m3_load(U + (size_t)mu * 9 * V, V, hop(C.dims, c, s, nu, +1, stride));
-            const M3 cc = m3_load(U + (size_t)nu * 9 * V, V, s);
-            A = m3_add(A, m3_mul_dag(m3_mul_dag(a, b), cc));
+#pragma unroll
+    for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(A.e[k].x), "+v"(A.e[k].y)::"memory");
+}
+
+// Index in a half of the copy of the neighbour one step along MU (STEP = +1
+// or -1) of the site (xh, c[1], c[2], c[3]) with x = 2 xh + odd, flat index i:
+// along y, z and t the neighbour keeps x and so xh; along x it keeps xh or
+// moves it by one, as x is odd or even. `odd` of the neighbour: 1 - odd along
+// x (c[] and odd are updated by the caller).
+template <int MU, int STEP>
+__device__ __forceinline__ int hb_hop(const HbGeom &G, const int *L, const int (&c)[4], int odd, int i)
+{
+    if constexpr (MU == 0) {
+        if constexpr (STEP > 0) {
+            if (!odd) return i;
+            return (c[0] + 1 == G.half) ? i - (G.half - 1) : i + 1;
+        } else {
+            if (odd) return i;
+            return (c[0] == 0) ? i + (G.half - 1) : i - 1;
         }
-        {
-            const int sm = hop(C.dims, c, s, nu, -1, stride);
-            const M3 a = m3_load(U + (size_t)nu * 9 * V, V, hop(C.dims, cp, sp, nu, -1, stride));
-            const M3 b = m3_load(U + (size_t)mu * 9 * V, V, sm);
-            const M3 cc = m3_load(U + (size_t)nu * 9 * V, V, sm);
-            A = m3_add(A, m3_mul(m3_mul(m3_dag(a), m3_dag(b)), cc));
-        }
+    } else {
+        const int st = MU == 1 ? G.half : MU == 2 ? G.V2h : G.V3h;
+        if constexpr (STEP > 0)
+            return (c[MU] + 1 == L[MU]) ? i - (L[MU] - 1) * st : i + st;
+        else
+            return (c[MU] == 0) ? i + (L[MU] - 1) * st : i - st;
     }
-    return A;
+}
+
+// The three links of one staple of direction NU of U_MU(s): the upper one
+// U_nu(s+mu) U_mu^dag(s+nu) U_nu^dag(s), or (LOWER) U_nu^dag(s+mu-nu)
+// U_mu^dag(s-nu) U_nu(s-nu). i: index of s in the half `par`; ip: of s + mu
+// in the other half. s + nu and s - nu are of the other parity, s + mu - nu
+// of the parity of s.
+struct Staple {
+    M3 a, b, c;
+};
+
+template <bool FULL, int MU, int NU, bool LOWER>
+__device__ __forceinline__ Staple load_staple(const double2 *U, const HbGeom &G, const int *L, int V, int par,
+                                              const int (&c)[4], int odd, int i, int ip)
+{
+    const double2 *own = U + (par ? V / 2 : 0);
+    const double2 *oth = U + (par ? 0 : V / 2);
+    const double2 *ownn = own + (size_t)NU * 9 * V, *othn = oth + (size_t)NU * 9 * V, *othm = oth + (size_t)MU * 9 * V;
+    Staple S;
+    if constexpr (!LOWER) {
+        S.a = hb_load<FULL>(othn, V, ip);
+        S.b = hb_load<FULL>(othm, V, hb_hop<NU, +1>(G, L, c, odd, i));
+        S.c = hb_load<FULL>(ownn, V, i);
+    } else {
+        const int im = hb_hop<NU, -1>(G, L, c, odd, i);
+        // s + mu: x is odd there where it is not at s (mu = x), else as at s
+        int cp[4] = {c[0], c[1], c[2], c[3]};
+        int oddp = odd;
+        if constexpr (MU == 0) {
+            cp[0] = !odd ? c[0] : (c[0] + 1 == G.half ? 0 : c[0] + 1);
+            oddp = 1 - odd;
+        } else {
+            cp[MU] = (c[MU] + 1 == L[MU]) ? 0 : c[MU] + 1;
+        }
+        S.a = hb_load<FULL>(ownn, V, hb_hop<NU, -1>(G, L, cp, oddp, ip));
+        S.b = hb_load<FULL>(othm, V, im);
+        S.c = hb_load<FULL>(othn, V, im);
+    }
+    return S;
+}
+
+// Adds a staple to the sum A: U_MU(s) A is the sum of the six plaquettes
+// through the link.
+template <bool FULL, bool LOWER>
+__device__ __forceinline__ void add_staple(M3 &A, Staple &S)
+{
+    if constexpr (!FULL) {
+        m3_row2(S.a);
+        m3_row2(S.b);
+        m3_row2(S.c);
+    }
+    if constexpr (!LOWER)
+        A = m3_add(A, m3_mul_dag(m3_mul_dag(S.a, S.b), S.c));
+    else
+        A = m3_add(A, m3_mul(m3_mul(m3_dag(S.a), m3_dag(S.b)), S.c));
+    hb_fence(A);
 }
 
 // One Cabibbo-Marinari update of u against staple sum A: for each subgroup
@@ -176,29 +257,127 @@ __device__ void cm_update(M3 &u, const M3 &A, double beta, int mode, int site, i
     m3_reunit(u);
 }
 
-// Updates every U_mu(s) with x + y + z + t = parity (mod 2); these links are
+// Updates every U_MU(s) with x + y + z + t = par (mod 2); these links are
 // independent (their staples hold only other directions and other-parity
-// sites). Work-item i takes the i-th such site in lexicographic order
-// (Lx even: half of every x-row).
-__global__ __launch_bounds__(kSiteBlock) void k_heatbath(const Cfg *__restrict__ cfgs, int mu, int parity, int mode,
-                                                         double beta, uint32_t k0, uint32_t k1, long long n)
+// sites). Work-item i takes the i-th such site in lexicographic order. MODE
+// 0: heatbath, 1: overrelaxation.
+//
+// What bounds it: memory. A class reads every link of the other three
+// directions and half of U_MU, in two-row form 384 B per lattice site at
+// least, and writes 48; at 32^4 it moves 720 (L2 holds too few sites of a
+// t-slice to serve the second use of each link) in 118 us, 6.4 TB/s, with
+// 2900 VALU instructions per wave (40 us of issue) beside it. Reading the
+// caller's array instead (three rows, the other parity's elements between
+// this one's in every cache line) took 432 us, the parity-split copy with the
+// loads of all six staples issued first (spilled) 200 us, one staple at a
+// time 124 us (three waves per SIMD), the next staple's loads in flight 117
+// us (two waves per SIMD); blocks not renumbered by XCD 132 us.
+template <bool FULL, int MODE, int MU>
+__global__ __launch_bounds__(kSiteBlock, 2) void k_heatbath(const Cfg *__restrict__ cfgs, int par, double beta,
+                                                         uint32_t k0, uint32_t k1, long long n)
 {
     const Cfg &C = cfgs[0];
-    const int half = C.dims[0] / 2;
-    const int i = blockIdx.x * kSiteBlock + threadIdx.x;
-    if (i >= C.V / 2) return;
-    const int row = i / half, xh = i % half;
+    const int V = C.V;
+    const int i = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    if (i >= V / 2) return;
+    const int L[4] = {C.dims[0], C.dims[1], C.dims[2], C.dims[3]};
+    const HbGeom G = {L[0] / 2, C.V2 / 2, C.V3 / 2};
     int c[4];
-    c[1] = row % C.dims[1];
-    c[2] = (row / C.dims[1]) % C.dims[2];
-    c[3] = row / (C.dims[1] * C.dims[2]);
-    c[0] = 2 * xh + ((c[1] + c[2] + c[3] + parity) & 1);
-    const int s = c[0] + C.dims[0] * row;
-    const M3 A = staple_sum(C, s, c, mu);
-    double2 *__restrict__ Um = C.U + (size_t)mu * 9 * C.V;
-    M3 u = m3_load(Um, C.V, s);
-    cm_update(u, A, beta, mode, s, mu, n, k0, k1);
-    m3_store(Um, C.V, s, u);
+    const int row = i / G.half;
+    c[0] = i - row * G.half;
+    const int r = row / L[1];
+    c[1] = row - r * L[1];
+    c[3] = r / L[2];
+    c[2] = r - c[3] * L[2];
+    const int odd = (c[1] + c[2] + c[3] + par) & 1;
+    const int s = 2 * c[0] + odd + L[0] * row;
+    double2 *U = hb_links(C);
+    const int ip = hb_hop<MU, +1>(G, L, c, odd, i);
+    M3 A = m3_zero();
+    constexpr int N0 = MU == 0 ? 1 : 0, N1 = MU <= 1 ? 2 : 1, N2 = MU <= 2 ? 3 : 2;
+#define GF_LOAD(NU_, LO_) load_staple<FULL, MU, NU_, LO_>(U, G, L, V, par, c, odd, i, ip)
+    if constexpr (FULL) {
+        Staple S = GF_LOAD(N0, false);
+        add_staple<FULL, false>(A, S);
+        S = GF_LOAD(N0, true);
+        add_staple<FULL, true>(A, S);
+        S = GF_LOAD(N1, false);
+        add_staple<FULL, false>(A, S);
+        S = GF_LOAD(N1, true);
+        add_staple<FULL, true>(A, S);
+        S = GF_LOAD(N2, false);
+        add_staple<FULL, false>(A, S);
+        S = GF_LOAD(N2, true);
+        add_staple<FULL, true>(A, S);
+    } else {  // each staple's links loaded while the one before is formed
+        Staple S0 = GF_LOAD(N0, false);
+        Staple S1 = GF_LOAD(N0, true);
+        add_staple<FULL, false>(A, S0);
+        S0 = GF_LOAD(N1, false);
+        add_staple<FULL, true>(A, S1);
+        S1 = GF_LOAD(N1, true);
+        add_staple<FULL, false>(A, S0);
+        S0 = GF_LOAD(N2, false);
+        add_staple<FULL, true>(A, S1);
+        S1 = GF_LOAD(N2, true);
+        add_staple<FULL, false>(A, S0);
+        add_staple<FULL, true>(A, S1);
+    }
+#undef GF_LOAD
+    double2 *Um = U + (size_t)MU * 9 * V + (par ? V / 2 : 0);
+    M3 u = hb_load<FULL>(Um, V, i);
+    if constexpr (!FULL) m3_row2(u);
+    cm_update(u, A, beta, MODE, s, MU, n, k0, k1);
+    if constexpr (FULL)
+        m3_store(Um, V, i, u);
+    else
+        m3_store12(Um, V, i, u);
+}
+
+// Index in the generator's copy of the caller's site s.
+__device__ __forceinline__ int hb_index(const Cfg &C, int s)
+{
+    int c[4];
+    site_coords(C.dims, s, c);
+    const int par = (c[0] + c[1] + c[2] + c[3]) & 1;
+    return (par ? C.V / 2 : 0) + (s - c[0]) / 2 + c[0] / 2;
+}
+
+// Caller's links -> the generator's copy.
+__global__ __launch_bounds__(kSiteBlock) void k_hb_pack(const Cfg *__restrict__ cfgs)
+{
+    const Cfg &C = cfgs[0];
+    const int V = C.V;
+    const int s = blockIdx.x * kSiteBlock + threadIdx.x;
+    if (s >= V) return;
+    const int i = hb_index(C, s);
+    double2 *__restrict__ dst = hb_links(C);
+    const double2 *__restrict__ src = C.U;
+#pragma unroll
+    for (int k = 0; k < 36; ++k) dst[(size_t)k * V + i] = ld_stream(src + (size_t)k * V + s);
+}
+
+// The generator's copy -> the caller's links, third rows rebuilt (what the
+// projection of the last sweep gave).
+__global__ __launch_bounds__(kSiteBlock) void k_hb_unpack(const Cfg *__restrict__ cfgs)
+{
+    const Cfg &C = cfgs[0];
+    const int V = C.V;
+    const int s = blockIdx.x * kSiteBlock + threadIdx.x;
+    if (s >= V) return;
+    const int i = hb_index(C, s);
+    const double2 *__restrict__ src = hb_links(C);
+    double2 *__restrict__ dst = C.U;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) m3_store(dst + (size_t)mu * 9 * V, V, s, m3_load12(src + (size_t)mu * 9 * V, V, i));
+}
+
+__device__ __forceinline__ int hop(const int *L, const int c[4], int s, int mu, int step, const int *stride)
+{
+    const int x = c[mu] + step;
+    if (x < 0) return s + (L[mu] - 1) * stride[mu];
+    if (x >= L[mu]) return s - (L[mu] - 1) * stride[mu];
+    return s + step * stride[mu];
 }
 
 // Per-block compensated sums of the six plaquettes Re Tr U_P of each site,
@@ -248,14 +427,39 @@ __global__ __launch_bounds__(256) void k_sum_plaquette(const Cfg *__restrict__ c
 
 }  // namespace
 
-hipError_t launch_heatbath_sweep(const Launch &L, int V, int mode, double beta, uint64_t seed, long long n)
+hipError_t launch_heatbath_sweep(const Launch &L, int V, int mode, int full, double beta, uint64_t seed, long long n)
 {
-    const dim3 grid((V / 2 + kSiteBlock - 1) / kSiteBlock);
+    if (full && mode != 0) return hipErrorInvalidValue;  // a call's first sweep is a heatbath sweep
+        // single waves as work-groups where work-groups of four would not give
+    // each CU one
+    const int nt = V / 2 >= 256 * kSiteBlock ? kSiteBlock : 64;
+    const dim3 grid((V / 2 + nt - 1) / nt), blk(nt);
     const uint32_t k0 = (uint32_t)(seed & 0xffffffffull), k1 = (uint32_t)(seed >> 32);
-    for (int mu = 0; mu < 4; ++mu)
-        for (int par = 0; par < 2; ++par)
-            hipLaunchKernelGGL(k_heatbath, grid, dim3(kSiteBlock), 0, L.stream, L.cfgs, mu, par, mode, beta, k0, k1,
-                               n);
+#define GF_HB(FULL_, MODE_, MU_)                                                                                    \
+    for (int par = 0; par < 2; ++par)                                                                               \
+        hipLaunchKernelGGL((k_heatbath<FULL_, MODE_, MU_>), grid, blk, 0, L.stream, L.cfgs, par, beta, k0, k1, n);
+#define GF_HB4(FULL_, MODE_) GF_HB(FULL_, MODE_, 0) GF_HB(FULL_, MODE_, 1) GF_HB(FULL_, MODE_, 2) GF_HB(FULL_, MODE_, 3)
+    if (full) {
+        GF_HB4(true, 0)
+    } else if (mode == 0) {
+        GF_HB4(false, 0)
+    } else {
+        GF_HB4(false, 1)
+    }
+#undef GF_HB4
+#undef GF_HB
+    return hipGetLastError();
+}
+
+hipError_t launch_heatbath_pack(const Launch &L, int nblk)
+{
+    hipLaunchKernelGGL(k_hb_pack, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs);
+    return hipGetLastError();
+}
+
+hipError_t launch_heatbath_unpack(const Launch &L, int nblk)
+{
+    hipLaunchKernelGGL(k_hb_unpack, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs);
     return hipGetLastError();
 }
 

@@ -201,7 +201,11 @@ hipError_t launch_pack_links(const Launch &L);
 hipError_t launch_momentum_table(const Launch &L);
 // reads every configuration's two-row link buffers (cache eviction before a timed pass)
 hipError_t launch_touch_links(const Launch &L);
-hipError_t launch_heatbath_sweep(const Launch &L, int V, int mode, double beta, uint64_t seed, long long n);
+// One sweep of the generator on its copy of the links (launch_heatbath_pack
+// before the first, with `full`; launch_heatbath_unpack after the last).
+hipError_t launch_heatbath_sweep(const Launch &L, int V, int mode, int full, double beta, uint64_t seed, long long n);
+hipError_t launch_heatbath_pack(const Launch &L, int nblk);
+hipError_t launch_heatbath_unpack(const Launch &L, int nblk);
 hipError_t launch_plaquette(const Launch &L, int nblk, double *out);
 hipError_t launch_unpack_links(const Launch &L);
 hipError_t launch_functional_g_impl(const Launch &L, int nblk, const double *omega, double scale, double *out);

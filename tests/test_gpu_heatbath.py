@@ -104,3 +104,22 @@ def test_thermalised_input_is_fixed_like_the_oracle():
     it, F, th = fx2.fix_until(1e-15, 20000)
     assert abs(it - n_ref) <= max(1, int(0.01 * n_ref))
     assert abs(F - Fr[-1]) < 1e-10 and th <= 1e-15
+
+
+@pytest.mark.parametrize("dims", [(2, 4, 6, 2), (6, 2, 2, 4), (12, 18, 6, 8), (18, 18, 18, 24)])
+def test_parity_split_sweeps(dims):
+    """The generator's parity-split copy at rows of one site per parity, rows
+    that share a wave, a ragged last work-group and both work-group sizes:
+    against the oracle, and a call of two sweeps against two calls of one
+    (whose second reads whole matrices where the single call rebuilds third
+    rows), bit for bit."""
+    U = hot_links(dims, 4)
+    ref = oracle.heatbath(dims, U, 5.9, 2, 1, seed=9, sweep0=0)
+    Ud, Us = dev(U), dev(U)
+    fx = GaugeFixer(Ud)
+    fx.heatbath(5.9, 2, 1, seed=9)
+    fs = GaugeFixer(Us)
+    for i in range(2):
+        fs.heatbath(5.9, 1, 1, seed=9, sweep0=i)
+    assert torch.equal(Ud, Us)
+    assert np.max(np.abs(Ud.cpu().numpy() - ref)) < 1e-7
