@@ -372,53 +372,108 @@ __global__ __launch_bounds__(kSiteBlock) void k_hb_unpack(const Cfg *__restrict_
     for (int mu = 0; mu < 4; ++mu) m3_store(dst + (size_t)mu * 9 * V, V, s, m3_load12(src + (size_t)mu * 9 * V, V, i));
 }
 
-__device__ __forceinline__ int hop(const int *L, const int c[4], int s, int mu, int step, const int *stride)
+// acc + Re Tr U_mu(x) U_nu(x+mu) U_mu^dag(x+nu) U_nu^dag(x): the scalar
+// product of two products of two links, a row at a time.
+__device__ __forceinline__ double plaq_pair(const M3 &um, const M3 &un, const M3 &un_mu, const M3 &um_nu, double acc)
 {
-    const int x = c[mu] + step;
-    if (x < 0) return s + (L[mu] - 1) * stride[mu];
-    if (x >= L[mu]) return s - (L[mu] - 1) * stride[mu];
-    return s + step * stride[mu];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            double2 a = cmul(um.e[i * 3], un_mu.e[j]), b = cmul(un.e[i * 3], um_nu.e[j]);
+            a = cfma(um.e[i * 3 + 1], un_mu.e[3 + j], a);
+            b = cfma(un.e[i * 3 + 1], um_nu.e[3 + j], b);
+            a = cfma(um.e[i * 3 + 2], un_mu.e[6 + j], a);
+            b = cfma(un.e[i * 3 + 2], um_nu.e[6 + j], b);
+            acc = fma(a.x, b.x, acc);
+            acc = fma(a.y, b.y, acc);
+        }
+    return acc;
 }
 
 // Per-block compensated sums of the six plaquettes Re Tr U_P of each site,
-// into partials[4 b], partials[4 b + 1] (the layout k_sum_partials reads).
-__global__ __launch_bounds__(kSiteBlock) void k_plaquette(const Cfg *__restrict__ cfgs)
+// into partials[2 b], partials[2 b + 1]. A block takes kSiteBlock consecutive
+// sites of the (x, y, z) volume (nb3 such sets) through tch t-slices. The
+// (i, t) plaquettes are completed one slice late, with the next slice's own
+// links, so that every block reads a slice's links in the same slice of its
+// walk as the blocks of its neighbours.
+//
+// What bounds it: memory. It cannot read less than the 576 B per site of the
+// links; at 32^4 it reads 1140 (the z neighbours of a slice, more than L2
+// holds apart) in 183 us, 6.5 TB/s. Before: two whole matrices loaded per
+// plaquette of every site and three products each, 440 us; own links once and
+// two products, one site per work-item without the walk, 251 us (1690 B per
+// site); the walk with the next slice's links kept for its own plaquettes 245
+// us (its neighbours read them a slice later, from memory).
+__global__ __launch_bounds__(kSiteBlock, 2) void k_plaquette(const Cfg *__restrict__ cfgs, int nb3, int tch)
 {
     __shared__ dd red[2 * (kSiteBlock / 64)];
     const Cfg &C = cfgs[0];
     const int V = C.V;
-    const int s = blockIdx.x * kSiteBlock + threadIdx.x;
-    double acc = 0.0;
-    if (s < V) {
-        int c[4];
-        site_coords(C.dims, s, c);
-        const int stride[4] = {1, C.dims[0], C.V2, C.V3};
-        for (int mu = 0; mu < 4; ++mu)
-            for (int nu = mu + 1; nu < 4; ++nu) {
-                const M3 a = m3_load(C.U + (size_t)mu * 9 * V, V, s);
-                const M3 b = m3_load(C.U + (size_t)nu * 9 * V, V, hop(C.dims, c, s, mu, +1, stride));
-                const M3 cc = m3_load(C.U + (size_t)mu * 9 * V, V, hop(C.dims, c, s, nu, +1, stride));
-                const M3 d = m3_load(C.U + (size_t)nu * 9 * V, V, s);
-                const M3 p = m3_mul_dag(m3_mul_dag(m3_mul(a, b), cc), d);
-                acc += p.e[0].x + p.e[4].x + p.e[8].x;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int tc = blk / nb3;
+    const int s3 = (blk - tc * nb3) * kSiteBlock + threadIdx.x;
+    dd sum = {0.0, 0.0}, zero = {0.0, 0.0};
+    if (s3 < C.V3) {
+        const int Lx = C.dims[0], Ly = C.dims[1], Lz = C.dims[2], Lt = C.dims[3];
+        const int r = s3 / Lx, x = s3 - r * Lx, z = r / Ly, y = r - z * Ly;
+        int f[3];  // forward neighbours in x, y, z
+        f[0] = (x + 1 == Lx) ? s3 - (Lx - 1) : s3 + 1;
+        f[1] = (y + 1 == Ly) ? s3 - (Ly - 1) * Lx : s3 + Lx;
+        f[2] = (z + 1 == Lz) ? s3 - (Lz - 1) * C.V2 : s3 + C.V2;
+        const double2 *U = C.U;
+        const double2 *Ut = U + (size_t)27 * V;
+        const int t0 = tc * tch;
+        M3 m[3];  // U_t^dag(x, t) U_i(x, t) U_t(x + i, t) of the slice before
+        for (int t = t0; t <= t0 + tch; ++t) {
+            const int ts = C.V3 * (t == Lt ? 0 : t);
+            double acc = 0.0;
+            M3 u[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                u[i] = hb_load<true>(U + (size_t)i * 9 * V, V, s3 + ts);
+                if (t > t0)  // the (i, t) plaquettes of the slice before
+#pragma unroll
+                    for (int k = 0; k < 9; ++k) {
+                        acc = fma(m[i].e[k].x, u[i].e[k].x, acc);
+                        acc = fma(m[i].e[k].y, u[i].e[k].y, acc);
+                    }
             }
+            if (t < t0 + tch) {
+                asm volatile("" : "+v"(acc)::"memory");
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int j = i + 1; j < 3; ++j) {
+                        acc = plaq_pair(u[i], u[j], hb_load<true>(U + (size_t)j * 9 * V, V, f[i] + ts),
+                                        hb_load<true>(U + (size_t)i * 9 * V, V, f[j] + ts), acc);
+                        asm volatile("" : "+v"(acc)::"memory");  // the next pair's loads after this one's products
+                    }
+                const M3 ut = hb_load<true>(Ut, V, s3 + ts);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    m[i] = m3_dag_mul(ut, m3_mul(u[i], hb_load<true>(Ut, V, f[i] + ts)));
+                    hb_fence(m[i]);
+                }
+            }
+            sum = dd_add(sum, dd{acc, 0.0});
+        }
     }
-    dd a = {acc, 0.0}, b = {0.0, 0.0};
-    block_sum2(a, b, red);
+    block_sum2(sum, zero, red);
     if (threadIdx.x == 0) {
-        double *p = C.partials + (size_t)blockIdx.x * 4;
-        p[0] = a.hi;
-        p[1] = a.lo;
+        double *p = C.partials + (size_t)blk * 2;
+        p[0] = sum.hi;
+        p[1] = sum.lo;
     }
 }
 
-__global__ __launch_bounds__(256) void k_sum_plaquette(const Cfg *__restrict__ cfgs, double *__restrict__ out)
+__global__ __launch_bounds__(256) void k_sum_plaquette(const Cfg *__restrict__ cfgs, int nblk, double *__restrict__ out)
 {
     __shared__ dd red[2 * (256 / 64)];
     const Cfg &C = cfgs[0];
     dd f = {0.0, 0.0}, z = {0.0, 0.0};
-    for (int i = threadIdx.x; i < C.nblk_site; i += blockDim.x) {
-        const double *p = C.partials + (size_t)i * 4;
+    for (int i = threadIdx.x; i < nblk; i += blockDim.x) {
+        const double *p = C.partials + (size_t)i * 2;
         f = dd_add(f, dd{p[0], p[1]});
     }
     block_sum2(f, z, red);
@@ -463,10 +518,11 @@ hipError_t launch_heatbath_unpack(const Launch &L, int nblk)
     return hipGetLastError();
 }
 
-hipError_t launch_plaquette(const Launch &L, int nblk, double *out)
+hipError_t launch_plaquette(const Launch &L, int nb3, int tch, int Lt, double *out)
 {
-    hipLaunchKernelGGL(k_plaquette, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs);
-    hipLaunchKernelGGL(k_sum_plaquette, dim3(1), dim3(256), 0, L.stream, L.cfgs, out);
+    const int nblk = nb3 * (Lt / tch);
+    hipLaunchKernelGGL(k_plaquette, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs, nb3, tch);
+    hipLaunchKernelGGL(k_sum_plaquette, dim3(1), dim3(256), 0, L.stream, L.cfgs, nblk, out);
     return hipGetLastError();
 }
 

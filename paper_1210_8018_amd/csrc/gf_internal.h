@@ -206,7 +206,9 @@ hipError_t launch_touch_links(const Launch &L);
 hipError_t launch_heatbath_sweep(const Launch &L, int V, int mode, int full, double beta, uint64_t seed, long long n);
 hipError_t launch_heatbath_pack(const Launch &L, int nblk);
 hipError_t launch_heatbath_unpack(const Launch &L, int nblk);
-hipError_t launch_plaquette(const Launch &L, int nblk, double *out);
+// nb3 site sets of kSiteBlock sites of the (x, y, z) volume, tch t-slices per
+// block (a divisor of Lt); needs 2 nb3 Lt / tch doubles of partials
+hipError_t launch_plaquette(const Launch &L, int nb3, int tch, int Lt, double *out);
 hipError_t launch_unpack_links(const Launch &L);
 hipError_t launch_functional_g_impl(const Launch &L, int nblk, const double *omega, double scale, double *out);
 hipError_t launch_functional_g_backward_impl(const Launch &L, int nblk, const double *omega, double scale,

@@ -136,6 +136,27 @@ int plan_tchunk(const int dims[4], int nb3, bool f64_links, int resident)
     return best;
 }
 
+// t-slices per block of the plaquette kernel: as above, and enough that the
+// blocks' sums (two doubles each) fit the 4 nblk_site doubles of partials
+// that every context has.
+int plan_plaquette_tch(const int dims[4], int nb3, int nblk_site, int resident)
+{
+    int best = 0;
+    double best_cost = 1e300;
+    for (int t = 1; t <= dims[3]; ++t) {
+        if (dims[3] % t) continue;
+        const long long nb = (long long)nb3 * (dims[3] / t);
+        if (nb > 2LL * nblk_site) continue;
+        if (best && t > kMaxTchunk) break;
+        const double cost = (double)((nb + resident - 1) / resident) * (t + 0.23);
+        if (!best || cost <= best_cost) {
+            best_cost = cost;
+            best = t;
+        }
+    }
+    return best;  // at least Lt itself: nb3 <= nblk_site
+}
+
 // In a batch every configuration's marching blocks take about the same
 // number of t-slices (the largest divisor of Lt up to GF_TCHUNK_BATCH,
 // default 4), so blocks carry equal work whatever lattice they belong to and
@@ -333,6 +354,7 @@ struct gf_ctx_s {
     Launch Lact{};                 // launch shapes of the active map
     std::vector<int> active;
     double *d_scalar = nullptr;
+    int ncu = 1;             // compute units of the device
     Ctrl *h_ctrl = nullptr;  // pinned mirror, ncfg entries
     std::vector<std::vector<double>> histF, histT;
     hipGraphExec_t gexec = nullptr;
@@ -1220,6 +1242,15 @@ gf_status choose_schedule(gf_ctx c, int requested)
     return GF_OK;
 }
 
+gf_status read_ncu(gf_ctx c)
+{
+    int dev = 0;
+    HIPCHK(c, hipGetDevice(&dev));
+    HIPCHK(c, hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    if (c->ncu < 1) c->ncu = 1;
+    return GF_OK;
+}
+
 gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links, void *d_ws, size_t ws_bytes,
                 void *stream)
 {
@@ -1239,10 +1270,8 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
     c->histT.assign(ncfg, {});
     c->kt.resize(K_N);
     for (int k = 0; k < K_N; ++k) c->kt[k].name = kNames[k];
-    int dev = 0, ncu = 0;
-    HIPCHK(c, hipGetDevice(&dev));
-    HIPCHK(c, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    if (ncu < 1) ncu = 1;
+    gf_status st0 = read_ncu(c);
+    if (st0 != GF_OK) return st0;
 
     size_t o = 0;
     c->d_cfgs = (Cfg *)(c->ws + o);
@@ -1277,7 +1306,7 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
         C.nblk_site = (C.V + kSiteBlock - 1) / kSiteBlock;
         C.nb3 = plan_tile(p.dims, C.tile, C.ntile);
         C.tch = (ncfg > 1) ? plan_tchunk_batch(p.dims)
-                           : plan_tchunk(p.dims, C.nb3, p.link_prec == 0, kMarchResidentPerCU * ncu);
+                           : plan_tchunk(p.dims, C.nb3, p.link_prec == 0, kMarchResidentPerCU * c->ncu);
         C.nblk_march = C.nb3 * (p.dims[3] / C.tch);
         C.U = (double2 *)links[k];
         C.U12[0] = (double2 *)(c->ws + l.links12a);
@@ -1395,6 +1424,8 @@ gf_status setup_functional(gf_ctx c, const gf_params *p, void *links, void *d_ws
     o += align_up(sizeof(Batch));
     c->d_scalar = (double *)(c->ws + o);
     o += align_up(64);
+    gf_status st = read_ncu(c);
+    if (st != GF_OK) return st;
     const FnLayout l = fn_layout(*p);
     c->cfg.assign(1, Cfg{});
     Cfg &C = c->cfg[0];
@@ -1729,7 +1760,9 @@ gf_status gf_plaquette(gf_ctx c, double *P)
     if (!c || !P) return GF_ERR_ARG;
     if (c->batch) return GF_ERR_STATE;
     const Cfg &C = c->cfg[0];
-    HIPCHK(c, launch_plaquette(c->L, C.nblk_site, c->d_scalar));
+    const int nb3 = (C.V3 + kSiteBlock - 1) / kSiteBlock;
+    const int tch = plan_plaquette_tch(C.dims, nb3, C.nblk_site, kMarchResidentPerCU * c->ncu);
+    HIPCHK(c, launch_plaquette(c->L, nb3, tch, C.dims[3], c->d_scalar));
     double h = 0.0;
     HIPCHK(c, hipMemcpyAsync(&h, c->d_scalar, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));

@@ -123,3 +123,22 @@ def test_parity_split_sweeps(dims):
         fs.heatbath(5.9, 1, 1, seed=9, sweep0=i)
     assert torch.equal(Ud, Us)
     assert np.max(np.abs(Ud.cpu().numpy() - ref)) < 1e-7
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (3, 4, 6, 2), (8, 8, 4, 6), (9, 12, 4, 27), (24, 16, 12, 8)])
+def test_plaquette_walks(dims):
+    """Less than a site set, ragged and whole sets, one and several slices per
+    walk; matrices that are not special unitary (every element counts). Error
+    bound: 64-bit sums of products of O(1) entries."""
+    U = hot_links(dims, 3) * np.exp(0.3j)
+    U[0, 1, 2] *= 1.5
+    ref = oracle.plaquette(dims, U)
+    Ud = dev(U)
+    fx = GaugeFixer(Ud)
+    assert abs(fx.plaquette() - ref) < 1e-13
+    # the functional-only context has fewer partial sums
+    p = gf.make_params(dims)
+    ws = torch.empty(gf.gf_workspace_bytes_functional(p), dtype=torch.uint8, device="cuda")
+    ctx = gf.gf_init_functional(p, Ud, ws)
+    assert abs(gf.gf_plaquette(ctx) - ref) < 1e-13
+    gf.gf_destroy(ctx)
