@@ -4,11 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgfix.so")
-SOURCES = ["gf_kernels.hip", "gf_heatbath.hip", "gf_runtime.hip"]
+SOURCES = ["gf_kernels.hip", "gf_fft_any.hip", "gf_heatbath.hip", "gf_runtime.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -16,7 +18,6 @@ FLAGS = [
     "-std=c++17",
     "--offload-arch=gfx950",
     "-fPIC",
-    "-shared",
     # no packed-FP32 instructions anywhere (they are not used deliberately)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # a multiply-add is fused only where one source expression holds it, so
@@ -27,13 +28,20 @@ FLAGS = [
 ]
 
 
-def build(verbose: bool = False) -> str:
-    srcs = [os.path.join(CSRC, s) for s in SOURCES]
-    tmp = LIB + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-o", tmp, *srcs]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+
+
+def build(verbose: bool = False) -> str:
+    tmp = LIB + ".tmp"
+    with tempfile.TemporaryDirectory() as d, ThreadPoolExecutor(len(SOURCES)) as pool:
+        objs = [os.path.join(d, s + ".o") for s in SOURCES]
+        jobs = [[HIPCC, *FLAGS, "-c", "-o", o, os.path.join(CSRC, s)] for s, o in zip(SOURCES, objs)]
+        for f in [pool.submit(_run, j, verbose) for j in jobs]:
+            f.result()
+        _run([HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", tmp, *objs], verbose)
     os.replace(tmp, LIB)
     return LIB
 

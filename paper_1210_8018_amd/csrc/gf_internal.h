@@ -51,6 +51,29 @@ __host__ __device__ constexpr int zt_shape_bit(int Lz, int Lt)
                                     : -1;
 }
 
+// Lines of gf_fft_any.hip: lengths up to 64, each a group of any_g1 points
+// and (where that is not the whole line) one of L / any_g1 points, run in the
+// registers of a work-item. The groups are consecutive stages of the radix
+// sequence 3, ..., 8, ..., 4 or 2 (FP64: also 4 4, 3 2 3 2 and 3 2 8, whose
+// groups need fewer registers).
+__host__ __device__ constexpr bool any_len_ok(int L)
+{
+    return L == 2 || L == 3 || L == 4 || L == 6 || L == 8 || L == 9 || L == 12 || L == 16 || L == 18 || L == 24 ||
+           L == 27 || L == 32 || L == 36 || L == 48 || L == 54 || L == 64;
+}
+__host__ __device__ constexpr int any_g1(int L, bool f64)
+{
+    return f64 && L == 16                                  ? 4
+           : f64 && (L == 36 || L == 48)                   ? 6
+           : (L <= 12 || L == 16)                          ? L
+           : (L == 18 || L == 24 || L == 27 || L == 48)    ? 3
+           : (L == 32 || L == 64)                          ? 8
+                                                           : 9;
+}
+// lines per work-group of the 1D passes: 256 where a work-item takes a whole
+// line, else as many as keep 4 FP64 tiles of the longest lines in LDS
+__host__ __device__ constexpr int any_line_width(int L, bool f64) { return any_g1(L, f64) == L ? 256 : 32; }
+
 // Transform schedules: which passes make up the 4D transform, scaling and
 // inverse (the scaling is always fused into the pass that completes the
 // forward transform).
@@ -121,6 +144,8 @@ struct Cfg {
     int ztPad;            // LDS elements added to every t-plane of a zt tile
     int zt_reg;           // the scaled (z, t) pass runs in registers: k_fft_zt_reg (32 x 32), k_fft_zt_lines (the others)
     int xy_reg;           // the iteration's (x, y) passes run in k_fft_xy_reg / k_fft_xy_inv_reg (Lx = Ly = 16 to 64)
+    int xy_any, zt_any;   // the 2D passes run in k_fft_xy_any / k_fft_zt_any where not in the above
+    int lany[2];          // the 1D z / t passes run in k_fft_line_any
     int line[2];          // the 1D z (line[0]) / t (line[1]) passes run in k_fft_line (that extent 16 to 64)
 };
 
@@ -134,6 +159,7 @@ struct Batch {
     int off_fft[4][kMaxCfg + 1];
     int off_xy[kMaxCfg + 1];
     int off_zt[kMaxCfg + 1];
+    int off_lany[2][kMaxCfg + 1];  // k_fft_line_any work-groups per field of the z and t passes
     int off_line[2][kMaxCfg + 1];  // k_fft_line units (64 / line_lanes xy-sites x 4 lines) of the z and t passes
 };
 
@@ -155,11 +181,15 @@ struct Launch {
     int ax_p2[4], ax_gen[4];       // same for the 1D passes of each axis
     int xy_tw2, xy_tw_total;       // LDS twiddle layout of the xy pass: y table offset, entries
     int zt_tw2, zt_tw_total;       // same for the zt pass
-    int zt_reg_any, zt_lds_any;    // scaled zt pass: some configuration in k_fft_zt_reg / in k_fft_zt
+    int zt_reg_any;                // scaled zt pass: some configuration in k_fft_zt_reg / k_fft_zt_lines
+    int xy_any, zt_any;            // some configuration has k_fft_xy_any / k_fft_zt_any passes
+    int xy_any_it, zt_any_it;      // ... in the iteration (not in the register passes there)
+    int xy_any_elems, zt_any_elems;  // LDS elements of their tiles and twiddles
+    int total_lany[2], lany_elems[2];  // work-groups per field and LDS elements of k_fft_line_any
     int zt_reg_groups;             // work-groups per tile of k_fft_zt_reg (1, 2 or 4: fields split among them)
     int zt_reg_p;                  // xy-sites per tile of k_fft_zt_reg / k_fft_zt_lines (2, 4 or 8)
     int zt_m;                      // (z, t) plane shapes of the register passes present (bits zt_shape_bit)
-    int xy_reg_any, xy_lds_any;    // iteration's xy passes: some configuration in the register / LDS-staged ones
+    int xy_reg_any;                // iteration's xy passes: some configuration in the register ones
     int xy_reg_groups;             // work-groups per tile of the register xy passes
     int xy_m;                      // their plane sizes present (bits line_len_bit)
     int total_line[2];             // k_fft_line units of the z and t passes (0: no configuration has them)
@@ -189,7 +219,16 @@ hipError_t launch_fft_xy_inv_gauge(const Launch &L, int respect_done, double2 *g
 hipError_t launch_fft_zt(const Launch &L, int mode, int sign, void *fields_override, int nfields, int respect_done);
 hipError_t launch_fft_zt_scale(const Launch &L, int respect_done);
 hipError_t set_lds_limits();
-hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override);
+// gf_fft_any.hip. to2: results to fields2; take_reg: also configurations whose
+// iteration runs this pass in k_fft_xy_reg / k_fft_xy_inv_reg
+hipError_t launch_fft_xy_any(const Launch &L, int sign, void *fields_override, int nfields, int respect_done, int to2,
+                             int take_reg, int fold);
+hipError_t launch_fft_zt_any(const Launch &L, int mode, int sign, void *fields_override, int nfields, int respect_done);
+hipError_t launch_fft_line_any(const Launch &L, int axis, int mode, int sign, void *fields_override, int nfields,
+                               int respect_done);
+hipError_t set_lds_limits_any();
+// from2: from the fields k_fft_xy_any left in fields2, for its configurations
+hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override, int from2 = 0);
 hipError_t launch_update(const Launch &L, int respect_done, const double2 *g_override);
 // Where the fused pass of an update takes the old links from and puts the
 // new ones (FP64 link storage): the two-row buffers, or the caller's array

@@ -10,6 +10,7 @@
 
 #include "gf_device.h"
 #include "gf_internal.h"
+#include "gf_transform.h"
 
 namespace gfk {
 
@@ -147,56 +148,6 @@ __global__ __launch_bounds__(kSiteBlock) void k_delta(const Cfg *__restrict__ cf
     }
 }
 
-// ============================================================ reductions + stopping rule
-// One block per configuration: sum the block partials in a fixed order,
-// F = sum/(12 V) (Eq. 1), theta = sum/(3 V) (Eq. 4); with count_iter, count
-// the update, record the history and evaluate the stopping rule theta <= eps.
-// Sum the block partials of one configuration in a fixed order (the whole
-// block takes part), F = sum/(12 V) (Eq. 1), theta = sum/(3 V) (Eq. 4); with
-// count_iter, count the update, record the history, flip the link buffer if
-// asked and evaluate the stopping rule theta <= eps.
-// The partial sums are taken kReduceLanes at a time in a fixed order; a
-// larger work-group leaves its other work-items at zero, which adds nothing
-// (dd_add of an exact zero returns its other operand), so every caller forms
-// the same sums bit for bit.
-constexpr int kReduceLanes = 256;
-
-__device__ void finalize_config(const Cfg &C, int nparts, int count_iter, int flip, dd *red)
-{
-    Ctrl *ct = C.ctrl;
-    dd f = {0.0, 0.0}, t = {0.0, 0.0};
-    for (int i = threadIdx.x; i < nparts && (int)threadIdx.x < kReduceLanes; i += kReduceLanes) {
-        const double *p = C.partials + (size_t)i * 4;
-        f = dd_add(f, dd{p[0], p[1]});
-        t = dd_add(t, dd{p[2], p[3]});
-    }
-    block_sum2(f, t, red);
-    if (threadIdx.x == 0) {
-        const double F = (f.hi + f.lo) / (12.0 * (double)C.V);
-        const double th = (t.hi + t.lo) / (3.0 * (double)C.V);
-        ct->F = F;
-        ct->theta = th;
-        long long it = ct->iter;
-        if (count_iter) {
-            it += 1;
-            ct->iter = it;
-            if (flip) ct->cur ^= 1;
-        }
-        ct->hist[it % kHist][0] = F;
-        ct->hist[it % kHist][1] = th;
-        if (count_iter) {
-            int d = kRunning;
-            if (!isfinite(F) || !isfinite(th))
-                d = kNonFinite;
-            else if (!(th > ct->eps))
-                d = kConverged;
-            else if (it >= ct->max_iter)
-                d = kMaxIter;
-            ct->done = d;
-        }
-    }
-}
-
 // One block per configuration entry: finalize_config over the partials of
 // the divergence kernel.
 __global__ __launch_bounds__(kReduceLanes) void k_reduce(const Cfg *__restrict__ cfgs, const Batch *__restrict__ B,
@@ -208,137 +159,7 @@ __global__ __launch_bounds__(kReduceLanes) void k_reduce(const Cfg *__restrict__
     finalize_config(C, C.nblk_march, count_iter, flip, red);
 }
 
-// ============================================================ transform tiles
-template <typename T2>
-struct Cx;
-template <>
-struct Cx<double2> {
-    using T = double;
-    __device__ static double2 mk(double a, double b) { return make_double2(a, b); }
-};
-template <>
-struct Cx<float2> {
-    using T = float;
-    __device__ static float2 mk(float a, float b) { return make_float2(a, b); }
-};
-
-template <typename T2>
-__device__ __forceinline__ T2 t_add(T2 a, T2 b)
-{
-    T2 r;
-    r.x = a.x + b.x;
-    r.y = a.y + b.y;
-    return r;
-}
-template <typename T2>
-__device__ __forceinline__ T2 t_sub(T2 a, T2 b)
-{
-    T2 r;
-    r.x = a.x - b.x;
-    r.y = a.y - b.y;
-    return r;
-}
-template <typename T2>
-__device__ __forceinline__ T2 t_mul(T2 a, T2 b)
-{
-    T2 r;
-    r.x = a.x * b.x - a.y * b.y;
-    r.y = a.x * b.y + a.y * b.x;
-    return r;
-}
-// multiply by sign * i
-template <typename T2>
-__device__ __forceinline__ T2 t_mul_si(T2 a, int sign)
-{
-    T2 r;
-    if (sign < 0) {
-        r.x = a.y;
-        r.y = -a.x;
-    } else {
-        r.x = -a.y;
-        r.y = a.x;
-    }
-    return r;
-}
-
-// r-point DFTs, b_q = sum_m a_m exp(sign 2 pi i m q / r), in place.
-template <typename T2>
-__device__ __forceinline__ void dft2(T2 *a)
-{
-    T2 t = a[0];
-    a[0] = t_add(t, a[1]);
-    a[1] = t_sub(t, a[1]);
-}
-
-template <typename T2>
-__device__ __forceinline__ void dft3(T2 *a, int sign)
-{
-    using T = typename Cx<T2>::T;
-    const T h = (T)0.86602540378443864676;  // sqrt(3)/2
-    T2 s = t_add(a[1], a[2]);
-    T2 d = t_sub(a[1], a[2]);
-    T2 b0 = t_add(a[0], s);
-    T2 m;
-    m.x = a[0].x - (T)0.5 * s.x;
-    m.y = a[0].y - (T)0.5 * s.y;
-    // exp(sign 2 pi i/3) = -1/2 + sign i h: b1 = m + sign i h d, b2 = m - sign i h d
-    T2 r = t_mul_si(d, sign);
-    r.x *= h;
-    r.y *= h;
-    a[0] = b0;
-    a[1] = t_add(m, r);
-    a[2] = t_sub(m, r);
-}
-
-template <typename T2>
-__device__ __forceinline__ void dft4r(T2 &a0, T2 &a1, T2 &a2, T2 &a3, int sign)
-{
-    const T2 s02 = t_add(a0, a2), d02 = t_sub(a0, a2);
-    const T2 s13 = t_add(a1, a3), d13 = t_mul_si(t_sub(a1, a3), sign);
-    a0 = t_add(s02, s13);
-    a2 = t_sub(s02, s13);
-    a1 = t_add(d02, d13);
-    a3 = t_sub(d02, d13);
-}
-
-template <typename T2>
-__device__ __forceinline__ void dft4(T2 *a, int sign)
-{
-    dft4r(a[0], a[1], a[2], a[3], sign);
-}
-
-template <typename T2>
-__device__ __forceinline__ void dft8(T2 *a, int sign)
-{
-    using T = typename Cx<T2>::T;
-    const T r2 = (T)0.70710678118654752440;
-    T2 e0 = a[0], e1 = a[2], e2 = a[4], e3 = a[6];
-    T2 o0 = a[1], o1 = a[3], o2 = a[5], o3 = a[7];
-    dft4r(e0, e1, e2, e3, sign);
-    dft4r(o0, o1, o2, o3, sign);
-    // w^q, w = exp(sign 2 pi i / 8): w^1 = (1 + sign i) r2, w^2 = sign i, w^3 = (-1 + sign i) r2
-    T2 t1, t3;
-    {
-        const T2 si = t_mul_si(o1, sign);
-        t1.x = (o1.x + si.x) * r2;
-        t1.y = (o1.y + si.y) * r2;
-    }
-    const T2 t2 = t_mul_si(o2, sign);
-    {
-        const T2 si = t_mul_si(o3, sign);
-        t3.x = (si.x - o3.x) * r2;
-        t3.y = (si.y - o3.y) * r2;
-    }
-    a[0] = t_add(e0, o0);
-    a[4] = t_sub(e0, o0);
-    a[1] = t_add(e1, t1);
-    a[5] = t_sub(e1, t1);
-    a[2] = t_add(e2, t2);
-    a[6] = t_sub(e2, t2);
-    a[3] = t_add(e3, t3);
-    a[7] = t_sub(e3, t3);
-}
-
+// ============================================================ 1D transform tiles
 // One Stockham radix-R stage over P pencils of length L held in LDS.
 // Element l of pencil k sits at k*ks + l*ls. Output is in natural order.
 template <int R, typename T2>
@@ -685,7 +506,7 @@ __global__ __launch_bounds__(kFftThreads) void k_fft(const Cfg *__restrict__ cfg
     if (respect_done && C.ctrl->done) return;
     const FftAxis &A = C.ax[axis];
     if (P2 != is_p2(A.L)) return;  // the other instance takes it
-    if (axis >= 2 && C.line[axis - 2]) return;  // k_fft_line takes it
+    if (axis >= 2 && (C.line[axis - 2] || C.lany[axis - 2])) return;  // k_fft_line or k_fft_line_any takes it
     const int t = tile - B->off_fft[axis][c];
     const int L = A.L, P = A.P, n = P * L;
     T2 *buf0 = (T2 *)smem;
@@ -1060,8 +881,7 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(CAP / TH >= 
     const int c = find_cfg(B->off_xy, B->n, tile);
     const Cfg &C = cfgs[B->idx[c]];
     if (respect_done && C.ctrl->done) return;
-    if (P2 != xy_is_p2(C)) return;  // the other instance takes it
-    if (C.xy_reg && !fields_override) return;  // k_fft_xy_reg takes it
+    if (C.xy_any || P2 != xy_is_p2(C)) return;  // k_fft_xy_any or the other instance takes it
     const int t = tile - B->off_xy[c];
     const int n = C.xyQ * C.V2;
     T2 *buf = (T2 *)smem;
@@ -1106,8 +926,7 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(CAP / TH >= 
     const int c = find_cfg(B->off_zt, B->n, tile);
     const Cfg &C = cfgs[B->idx[c]];
     if (respect_done && C.ctrl->done) return;
-    if (P2 != zt_is_p2(C)) return;  // the other instance takes it
-    if (mode == 1 && C.zt_reg) return;  // k_fft_zt_reg takes it
+    if (C.zt_any || P2 != zt_is_p2(C)) return;  // k_fft_zt_any or the other instance takes it
     const int t = tile - B->off_zt[c];
     const int P = C.ztP, Lz = C.dims[2], Lt = C.dims[3], V2 = C.V2;
     const int n = P * Lz * Lt;
@@ -1969,18 +1788,30 @@ __device__ __forceinline__ void store_gauge(const Cfg &C, double2 *g_override, i
         m3_store(C.g, C.V, s, m);
 }
 
+// Whether the register inverse (x, y) pass does the gauge step of a
+// configuration that has it: it writes the filtered fields (two_row 3) or,
+// from the FP32 transform, binary32 g (2), not a caller's full matrices.
+template <typename T2>
+__host__ __device__ constexpr bool reg_forms_g(const double2 *g_override, int two_row)
+{
+    return !g_override && (two_row == 3 || (two_row == 2 && std::is_same<T2, float2>::value));
+}
+
 template <typename T2>
 __global__ __launch_bounds__(kSiteBlock) void k_gauge(const Cfg *__restrict__ cfgs, const Batch *__restrict__ B,
-                                                      int respect_done, double2 *__restrict__ g_override, int two_row)
+                                                      int respect_done, double2 *__restrict__ g_override, int two_row,
+                                                      int from2)
 {
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     const int c = find_cfg(B->off_site, B->n, blk);
     const Cfg &C = cfgs[B->idx[c]];
     if (respect_done && C.ctrl->done) return;
+    // from2: after k_fft_xy_any; the others' inverse pass has formed g
+    if (from2 && (!C.xy_any || (C.xy_reg && reg_forms_g<T2>(g_override, two_row)))) return;
     const int V = C.V;
     const int s = (blk - B->off_site[c]) * kSiteBlock + threadIdx.x;
     if (s >= V) return;
-    const T2 *__restrict__ f = (const T2 *)C.fields;
+    const T2 *__restrict__ f = (const T2 *)(from2 ? C.fields2 : C.fields);
     if (two_row == 3 && !g_override) {  // the fused pass forms g itself
         T2 *__restrict__ o = (T2 *)C.fields2;
 #pragma unroll
@@ -2008,9 +1839,7 @@ __global__ __launch_bounds__(TH) void k_fft_xy_inv_gauge(const Cfg *__restrict__
     const int c = find_cfg(B->off_xy, B->n, tile);
     const Cfg &C = cfgs[B->idx[c]];
     if (respect_done && C.ctrl->done) return;
-    if (P2 != xy_is_p2(C)) return;  // the other instance takes it
-    // k_fft_xy_inv_reg takes it
-    if (C.xy_reg && !g_override && (two_row == 3 || (two_row == 2 && std::is_same<T2, float2>::value))) return;
+    if (C.xy_any || P2 != xy_is_p2(C)) return;  // k_fft_xy_any or the other instance takes it
     const int t = tile - B->off_xy[c];
     const int n = C.xyQ * C.V2;
     const size_t site0 = (size_t)t * n;
@@ -2794,7 +2623,11 @@ hipError_t launch_fft_axis(const Launch &L, int axis, int sign, int mode, void *
 #undef GF_LINE_L
 #undef GF_LINE_K
     }
-    if (L.total_fft_tiles[axis] == 0) return hipGetLastError();  // every configuration in k_fft_line
+    if (axis >= 2 && L.total_lany[axis - 2] > 0) {
+        const hipError_t e = launch_fft_line_any(L, axis, mode, sign, fields_override, nfields, respect_done);
+        if (e != hipSuccess) return e;
+    }
+    if (L.total_fft_tiles[axis] == 0) return hipGetLastError();  // every configuration in the above
     const dim3 grid(L.total_fft_tiles[axis], nfields);
     // power-of-two and general instances, as for the 2D passes
     const size_t sh32 = (size_t)(2 * L.max_lds_elems + 256) * sizeof(float2);
@@ -2861,10 +2694,17 @@ static hipError_t run_xy(const Launch &L, int nf, int sign, void *fo, int rd, in
     }
         GF_XYR(16) GF_XYR(24) GF_XYR(32) GF_XYR(48) GF_XYR(64)
 #undef GF_XYR
-        if (!L.xy_lds_any) return hipGetLastError();
     }
-    // a batch mixing power-of-two and general extents launches both
-    // instances; only the first carries the folded reduction
+    if (fo ? L.xy_any : L.xy_any_it) {
+        const int f = fold;
+        fold = 0;
+        const hipError_t e = launch_fft_xy_any(L, sign, fo, nf, rd, 0, fo != nullptr, f);
+        if (e != hipSuccess) return e;
+        ++launched;
+    }
+    // extents above 64; a batch mixing power-of-two and general extents
+    // launches both instances; only the first launch carries the folded
+    // reduction
 #define X(C_, T_, P2_)                                                                                            \
     if (L.xy_cap == C_ && L.xy_th == T_ && (P2_ ? L.xy_p2 : L.xy_gen)) {                                          \
         const int f = fold;                                                                                       \
@@ -2909,7 +2749,11 @@ static hipError_t run_zt(const Launch &L, int nf, int mode, int sign, void *fo, 
         GF_ZTL(16, 32, 2) GF_ZTL(16, 32, 4) GF_ZTL(16, 32, 8) GF_ZTL(48, 48, 2)
 #undef GF_ZTL
         ++launched;
-        if (!L.zt_lds_any) return hipGetLastError();
+    }
+    if (mode == 1 ? L.zt_any_it : L.zt_any) {
+        const hipError_t e = launch_fft_zt_any(L, mode, sign, fo, nf, rd);
+        if (e != hipSuccess) return e;
+        ++launched;
     }
 #define X(C_, T_, P2_)                                                                                            \
     if (L.zt_cap == C_ && L.zt_th == T_ && (P2_ ? L.zt_p2 : L.zt_gen)) {                                          \
@@ -2930,7 +2774,8 @@ static hipError_t run_xyg(const Launch &L, int rd, double2 *go)
     // the register pass writes the filtered fields (FP64 link storage) or,
     // from the FP32 transform, binary32 g (single-precision storage)
     const int gm = gauge_store_mode(L);
-    if (!go && L.xy_reg_any && (gm == 3 || (gm == 2 && std::is_same<T2, float2>::value))) {
+    const bool reg = reg_forms_g<T2>(go, gm);
+    if (L.xy_reg_any && reg) {
 #define GF_XYR(L_, S_, NG_)                                                                                        \
     if (L.xy_m & (1 << line_len_bit(L_))) {                                                                        \
         hipLaunchKernelGGL((k_fft_xy_inv_reg<T2, L_, S_>), dim3(L.total_xy_tiles * (NG_)),                         \
@@ -2945,7 +2790,14 @@ static hipError_t run_xyg(const Launch &L, int rd, double2 *go)
             GF_XYR(16, 2, 1) GF_XYR(24, 2, 1) GF_XYR(32, 2, 1) GF_XYR(48, 2, 1) GF_XYR(64, 2, 1)
         }
 #undef GF_XYR
-        if (!L.xy_lds_any) return hipGetLastError();
+    }
+    // extents up to 64: the filtered fields, and g from them unless the fused
+    // pass forms it
+    if (reg ? L.xy_any_it : L.xy_any) {
+        hipError_t e = launch_fft_xy_any(L, +1, nullptr, kFields, rd, 1, !reg, 0);
+        if (e == hipSuccess && (go || gm != 3)) e = launch_gauge(L, rd, go, 1);
+        if (e != hipSuccess) return e;
+        ++launched;
     }
 #define X(C_, T_, P2_)                                                                                            \
     if (L.xy_cap == C_ && L.xy_th == T_ && (P2_ ? L.xy_p2 : L.xy_gen)) {                                          \
@@ -2970,8 +2822,8 @@ bool can_fold_reduce(const Launch &L)
     if (xy_reg_threads<48>() >= kReduceLanes) big |= 1 << line_len_bit(48);
     if (xy_reg_threads<64>() >= kReduceLanes) big |= 1 << line_len_bit(64);
     const bool reg = L.xy_reg_any && (L.xy_m & big);
-    const bool lds = L.xy_lds_any && L.xy_th >= kReduceLanes;
-    return reg || lds;
+    const bool lds = (L.xy_p2 || L.xy_gen) && L.xy_th >= kReduceLanes;
+    return reg || lds || L.xy_any_it;
 }
 
 hipError_t launch_fft_xy(const Launch &L, int sign, void *fields_override, int nfields, int respect_done,
@@ -3056,18 +2908,18 @@ static hipError_t set_lds_t()
 hipError_t set_lds_limits()
 {
     hipError_t e = set_lds_t<double2>();
-    if (e != hipSuccess) return e;
-    return set_lds_t<float2>();
+    if (e == hipSuccess) e = set_lds_t<float2>();
+    return e == hipSuccess ? set_lds_limits_any() : e;
 }
 
-hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override)
+hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override, int from2)
 {
     if (L.fp32)
         hipLaunchKernelGGL(k_gauge<float2>, dim3(L.total_site_blocks), dim3(kSiteBlock), 0, L.stream, L.cfgs,
-                           L.batch, respect_done, g_override, gauge_store_mode(L));
+                           L.batch, respect_done, g_override, gauge_store_mode(L), from2);
     else
         hipLaunchKernelGGL(k_gauge<double2>, dim3(L.total_site_blocks), dim3(kSiteBlock), 0, L.stream, L.cfgs,
-                           L.batch, respect_done, g_override, gauge_store_mode(L));
+                           L.batch, respect_done, g_override, gauge_store_mode(L), from2);
     return hipGetLastError();
 }
 

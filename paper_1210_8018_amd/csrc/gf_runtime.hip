@@ -187,6 +187,29 @@ int plan_ztP(const int dims[4], int target)
     return P;
 }
 
+// Tiles of the passes of gf_fft_any.hip (one field each). xy: as many planes
+// as the target holds, fewer while that leaves the device without `want`
+// work-groups and a tile has 256 elements to spare.
+int plan_any_xyQ(const int dims[4], int target, int want)
+{
+    const int V2 = dims[0] * dims[1], planes = dims[2] * dims[3];
+    int Q = std::max(1, std::min(planes, target / V2));
+    while (Q > 1 && kFields * ((planes + Q - 1) / Q) < want && Q * V2 > 512) Q = (Q + 1) / 2;
+    return Q;
+}
+
+// zt: P xy-sites (a power of two), up to a 128-byte line, within the target;
+// past the target, up to 64 KiB of LDS, while a row is less than 64 bytes;
+// fewer while that leaves the device without `want` work-groups.
+int plan_any_ztP(const int dims[4], int target, int csz, int want)
+{
+    const int V2 = dims[0] * dims[1], n = dims[2] * dims[3];
+    int P = 1;
+    while (P < V2 && P * csz < 128 && (2 * P * n <= target || (P * csz < 64 && 2 * P * n * csz <= 65536))) P *= 2;
+    while (P * csz > 64 && kFields * ((V2 + P - 1) / P) < want) P /= 2;
+    return P;
+}
+
 FftAxis plan_axis(const int dims[4], int mu)
 {
     FftAxis a{};
@@ -799,9 +822,11 @@ void fill_map(gf_ctx c, const std::vector<int> &list, Batch &b, Launch &L)
         // the z and t passes of a configuration's lines in registers run in
         // k_fft_line: 64 / line_lanes xy-sites times 4 lines per unit
         for (int mu = 0; mu < 4; ++mu)
-            b.off_fft[mu][e + 1] = b.off_fft[mu][e] + ((mu >= 2 && C.line[mu - 2]) ? 0 : C.ax[mu].ntile);
+            b.off_fft[mu][e + 1] = b.off_fft[mu][e] + ((mu >= 2 && (C.line[mu - 2] || C.lany[mu - 2])) ? 0 : C.ax[mu].ntile);
         for (int a = 0; a < 2; ++a) {
             const int nq = 64 / line_lanes(C.dims[2 + a]);
+            const int w = any_line_width(C.dims[2 + a], !c->L.fp32), nlines = C.V / C.dims[2 + a];
+            b.off_lany[a][e + 1] = b.off_lany[a][e] + (C.lany[a] ? (nlines + w - 1) / w : 0);
             b.off_line[a][e + 1] = b.off_line[a][e] + (C.line[a] ? (C.V2 / nq) * (C.dims[3 - a] / 4) : 0);
         }
         b.off_xy[e + 1] = b.off_xy[e] + C.nxy;
@@ -835,6 +860,7 @@ void fill_map(gf_ctx c, const std::vector<int> &list, Batch &b, Launch &L)
     L.total_xy_tiles = b.off_xy[b.n];
     for (int a = 0; a < 2; ++a) {
         L.total_line[a] = b.off_line[a][b.n];
+        L.total_lany[a] = b.off_lany[a][b.n];
         L.line_m[a] = 0;
         for (int e = 0; e < b.n; ++e)
             if (c->cfg[list[e]].line[a]) L.line_m[a] |= 1 << line_len_bit(c->cfg[list[e]].dims[2 + a]);
@@ -848,23 +874,30 @@ void fill_map(gf_ctx c, const std::vector<int> &list, Batch &b, Launch &L)
     // not launched)
     auto p2 = [](int v) { return (v & (v - 1)) == 0; };
     L.xy_p2 = L.xy_gen = L.zt_p2 = L.zt_gen = 0;
-    L.xy_reg_any = L.xy_lds_any = L.zt_reg_any = L.zt_lds_any = 0;
+    L.xy_reg_any = L.zt_reg_any = 0;
+    L.xy_any = L.zt_any = L.xy_any_it = L.zt_any_it = 0;
     L.xy_m = L.zt_m = 0;
     for (int mu = 0; mu < 4; ++mu) L.ax_p2[mu] = L.ax_gen[mu] = 0;
     for (int e = 0; e < b.n; ++e) {
         const Cfg &C = c->cfg[list[e]];
-        if (C.nxy) {
+        if (C.xy_any)
+            L.xy_any = 1, L.xy_any_it |= !C.xy_reg;
+        else if (C.nxy)
             ((p2(C.dims[0]) && p2(C.dims[1]) && p2(C.xyQ)) ? L.xy_p2 : L.xy_gen) = 1;
-            (C.xy_reg ? L.xy_reg_any : L.xy_lds_any) = 1;
-            if (C.xy_reg) L.xy_m |= 1 << line_len_bit(C.dims[0]);
+        if (C.xy_reg) {
+            L.xy_reg_any = 1;
+            L.xy_m |= 1 << line_len_bit(C.dims[0]);
         }
-        if (C.nzt) {
+        if (C.zt_any)
+            L.zt_any = 1, L.zt_any_it |= !C.zt_reg;
+        else if (C.nzt)
             ((p2(C.dims[2]) && p2(C.dims[3])) ? L.zt_p2 : L.zt_gen) = 1;
-            (C.zt_reg ? L.zt_reg_any : L.zt_lds_any) = 1;
-            if (C.zt_reg) L.zt_m |= 1 << zt_shape_bit(C.dims[2], C.dims[3]);
+        if (C.zt_reg) {
+            L.zt_reg_any = 1;
+            L.zt_m |= 1 << zt_shape_bit(C.dims[2], C.dims[3]);
         }
         for (int mu = 0; mu < 4; ++mu) {
-            if (mu >= 2 && C.line[mu - 2]) continue;
+            if (mu >= 2 && (C.line[mu - 2] || C.lany[mu - 2])) continue;
             (p2(C.dims[mu]) ? L.ax_p2[mu] : L.ax_gen[mu]) = 1;
         }
     }
@@ -888,21 +921,33 @@ gf_status apply_schedule(gf_ctx c, int sched, const Tiles &tl)
 {
     for (int k = 0; k < c->ncfg; ++k) {
         Cfg &C = c->cfg[k];
-        C.xyQ = xy_feasible(C.dims) ? plan_xyQ(C.dims, tl.xy_target) : 1;
+        const bool fit_xy = xy_feasible(C.dims), fit_zt = zt_feasible(C.dims);
+        const int csz = c->L.fp32 ? 8 : 16;
+        C.xy_any = fit_xy && any_len_ok(C.dims[0]) && any_len_ok(C.dims[1]);
+        C.zt_any = fit_zt && any_len_ok(C.dims[2]) && any_len_ok(C.dims[3]);
+        C.xyQ = C.xy_any ? plan_any_xyQ(C.dims, tl.xy_target, 2 * c->ncu / c->ncfg)
+                : fit_xy ? plan_xyQ(C.dims, tl.xy_target)
+                         : 1;
         C.xy_reg = ((sched == kSchedXYZT || sched == kSchedXY1D) && tl.xy_reg && xy_reg_fits(C)) ? 1 : 0;
         // every 1D z and t pass (those of schedules 1 and 2, and the plain
         // transform calls)
-        for (int a = 0; a < 2; ++a) C.line[a] = (tl.line_reg && line_fits(C, a)) ? 1 : 0;
+        for (int a = 0; a < 2; ++a) {
+            C.line[a] = (tl.line_reg && line_fits(C, a)) ? 1 : 0;
+            C.lany[a] = !C.line[a] && any_len_ok(C.dims[2 + a]);
+        }
         if (C.xy_reg) C.xyQ = xy_reg_planes_for(C.dims[0]);  // the register passes' tile
-        C.nxy = xy_feasible(C.dims) ? (C.dims[2] * C.dims[3]) / C.xyQ : 0;
-        C.ztP = zt_feasible(C.dims) ? plan_ztP(C.dims, tl.zt_target) : 1;
+        C.nxy = fit_xy ? (C.dims[2] * C.dims[3] + C.xyQ - 1) / C.xyQ : 0;
+        C.ztP = C.zt_any ? plan_any_ztP(C.dims, tl.zt_target, csz, 2 * c->ncu / c->ncfg)
+                : fit_zt ? plan_ztP(C.dims, tl.zt_target)
+                         : 1;
         // the register pass's tile: zt_reg_p xy-sites (one width per
-        // launch); a configuration whose Lx Ly it does not divide takes the
-        // LDS-staged pass
+        // launch); a configuration whose Lx Ly it does not divide takes
+        // another pass
         C.zt_reg = (sched == kSchedXYZT && tl.zt_reg && zt_reg_fits(C, tl.zt_reg_p)) ? 1 : 0;
         if (C.zt_reg) C.ztP = tl.zt_reg_p;
-        C.nzt = zt_feasible(C.dims) ? C.V2 / C.ztP : 0;
-        // bank-spreading pads, kept inside the 1/8 slack of the LDS tile
+        C.nzt = fit_zt ? (C.V2 + C.ztP - 1) / C.ztP : 0;
+        // bank-spreading pads of the LDS-staged passes, kept inside the 1/8
+        // slack of their tile
         const int xycap = C.xyQ * C.V2 <= 1024 ? 1024 : (C.xyQ * C.V2 <= 2048 ? 2048 : 4096);
         C.xyPad = (C.dims[1] * C.xyQ <= xycap / 8) ? 1 : 0;
         // zt tile: t-planes Tp = P Lz + ztPad elements apart with Tp = P (mod
@@ -915,17 +960,28 @@ gf_status apply_schedule(gf_ctx c, int sched, const Tiles &tl)
         int zp = ((r % 32) + 32) % 32;
         if (zp * C.dims[3] > ztcap / 8) zp = ((r % 16) + 16) % 16;
         C.ztPad = (zp * C.dims[3] <= ztcap / 8) ? zp : 0;
+        if (C.zt_any) {
+            const int m = 256 / csz;
+            C.ztPad = ((r % m) + m) % m;
+        }
     }
     std::vector<int> all(c->ncfg);
     for (int k = 0; k < c->ncfg; ++k) all[k] = k;
     fill_map(c, all, c->bmap, c->L);
     // tile capacities and twiddle layouts over every configuration (the
     // instance flags are set per launch list by fill_map)
-    int xy_max = 0, zt_max = 0, mx = 0, my = 0, mz = 0, mt = 0;
+    int xy_max = 0, zt_max = 0, mx = 0, my = 0, mz = 0, mt = 0, xa = 0, za = 0, la[2] = {0, 0};
     for (int k = 0; k < c->ncfg; ++k) {
         const Cfg &C = c->cfg[k];
-        if (C.nxy) xy_max = std::max(xy_max, C.xyQ * C.V2);
-        if (C.nzt) zt_max = std::max(zt_max, C.ztP * C.dims[2] * C.dims[3]);
+        if (C.nxy && !C.xy_any) xy_max = std::max(xy_max, C.xyQ * C.V2);
+        if (C.nzt && !C.zt_any) zt_max = std::max(zt_max, C.ztP * C.dims[2] * C.dims[3]);
+        if (C.xy_any) xa = std::max(xa, (C.dims[0] | 1) * C.dims[1] * C.xyQ + C.dims[0] + C.dims[1]);
+        if (C.zt_any) za = std::max(za, (C.ztP * C.dims[2] + C.ztPad) * C.dims[3] + C.dims[2] + C.dims[3]);
+        for (int a = 0; a < 2; ++a)
+            if (C.lany[a]) {
+                const int L = C.dims[2 + a];
+                la[a] = std::max(la[a], (any_g1(L, !c->L.fp32) == L ? 0 : any_line_width(L, !c->L.fp32) * L) + L);
+            }
         mx = std::max(mx, C.dims[0]);
         my = std::max(my, C.dims[1]);
         mz = std::max(mz, C.dims[2]);
@@ -943,6 +999,9 @@ gf_status apply_schedule(gf_ctx c, int sched, const Tiles &tl)
     // one after the other (the next one prefetched)
     c->L.xy_fpb = kFields;
     c->L.zt_fpb = kFields;
+    c->L.xy_any_elems = xa;
+    c->L.zt_any_elems = za;
+    for (int a = 0; a < 2; ++a) c->L.lany_elems[a] = la[a];
     c->L.xy_tw2 = mx;
     c->L.xy_tw_total = mx + my;
     c->L.zt_tw2 = mz;
@@ -1121,8 +1180,15 @@ gf_status choose_schedule(gf_ctx c, int requested)
     // tiles, or the register pass with 1, 2 or 4 (the LDS tile then serves
     // only the plain transform calls)
     std::vector<Tiles> xs, zs;
-    for (int xt : {1024, 4096})
+    bool old_xy = false, old_zt = false;  // extents above 64: the LDS-staged passes
+    for (int k = 0; k < c->ncfg; ++k) {
+        const int *d = c->cfg[k].dims;
+        old_xy = old_xy || !(any_len_ok(d[0]) && any_len_ok(d[1]));
+        old_zt = old_zt || !(any_len_ok(d[2]) && any_len_ok(d[3]));
+    }
+    for (int xt : {1024, 2048, 4096})
         for (int xe : {4, 8}) {
+            if (xe == 8 && !old_xy) continue;
             Tiles t;
             t.xy_target = xt;
             t.xy_ept = xe;
@@ -1135,8 +1201,9 @@ gf_status choose_schedule(gf_ctx c, int requested)
             t.xy_reg = g;
             xs.push_back(t);
         }
-    for (int zt : {2048, 4096})
+    for (int zt : {1024, 2048, 4096})
         for (int ze : {4, 8}) {
+            if (ze == 8 && !old_zt) continue;
             Tiles t;
             t.zt_target = zt;
             t.zt_ept = ze;

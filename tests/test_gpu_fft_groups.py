@@ -1,0 +1,43 @@
+"""Transform passes with register groups (extents up to 64) against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1210_8018_amd.api import GaugeFixer
+from paper_1210_8018_amd.inputs import random_links
+
+pytestmark = pytest.mark.gpu
+
+ALPHA = 0.08
+
+
+@pytest.mark.parametrize("dims", [(2, 3, 4, 6), (6, 9, 8, 12), (18, 16, 9, 27), (27, 24, 3, 36), (36, 4, 48, 2),
+                                  (54, 3, 2, 64), (64, 2, 54, 9), (9, 32, 18, 16), (3, 3, 32, 24), (48, 6, 6, 18),
+                                  (2, 2, 64, 4), (12, 54, 3, 8)])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("sched", [2, 3])
+def test_register_group_passes_match_oracle(dims, prec, sched):
+    """Every line length along every kind of axis, with ragged last tiles of
+    xy-sites (odd Lx Ly), of planes and of lines: plain transforms of one and
+    five fields, and the scaled transform inside the gauge vector. Bounds: the
+    FP64 ones of the other transform tests; FP32 transform, 3e-6 of the largest
+    coefficient, and for g the error of complex64 rounding through K(p)."""
+    V = int(np.prod(dims))
+    U = random_links(dims, 0.4, 43)
+    fx = GaugeFixer(torch.from_numpy(U).to("cuda"), fft_prec=prec, fft_schedule=sched)
+    g = fx.gauge().cpu().numpy()
+    gref = oracle.gauge_from_delta(dims, oracle.delta(dims, U), ALPHA)
+    p2max = sum(4 * np.sin(np.pi * (L // 2) / L) ** 2 for L in dims)
+    p2min = 4 * np.sin(np.pi / max(dims)) ** 2
+    tol_g = 32 * 2.0 ** -24 * max(1.0, ALPHA / 2 * p2max / p2min) if prec else 1e-13
+    assert np.max(np.abs(g - gref)) < tol_g
+    rng = np.random.default_rng(7)
+    ct = torch.complex64 if prec else torch.complex128
+    tol = 3e-6 if prec else 1e-13
+    for nf, sign in ((1, -1), (5, +1)):
+        f = rng.standard_normal((nf, V)) + 1j * rng.standard_normal((nf, V))
+        got = fx.fft(torch.from_numpy(f).to(ct).to("cuda").contiguous(), sign).cpu().numpy().astype(np.complex128)
+        for k in range(nf):
+            ref = oracle.fft4d(dims, f[k], sign)
+            assert np.max(np.abs(got[k] - ref)) < tol * np.max(np.abs(ref)), (sign, k)
