@@ -272,6 +272,15 @@ __device__ __forceinline__ M3 m3_identity()
     return c;
 }
 
+// Orders the terms of a sum of products: what is loaded after the fence is
+// issued after `m` is formed. Without it the compiler issues the loads of all
+// terms first, more than the registers hold, and spills.
+__device__ __forceinline__ void m3_fence(M3 &m)
+{
+#pragma unroll
+    for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(m.e[k].x), "+v"(m.e[k].y)::"memory");
+}
+
 // Rows 0 and 1 of a b c^dag, row 2 rebuilt as conj(r0 x r1): the product of
 // special unitary matrices is special unitary, so this is the full product up
 // to rounding, for two thirds of the multiplications.

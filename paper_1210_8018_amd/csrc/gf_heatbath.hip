@@ -120,15 +120,6 @@ __device__ __forceinline__ M3 hb_load(const double2 *base, int V, int s)
     return m;
 }
 
-// Orders the staples: what is loaded after the fence is issued after this
-// sum is formed. Without it the compiler issues the loads of all six staples
-// first (430 registers' worth), which spills.
-__device__ __forceinline__ void hb_fence(M3 &A)
-{
-#pragma unroll
-    for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(A.e[k].x), "+v"(A.e[k].y)::"memory");
-}
-
 // Index in a half of the copy of the neighbour one step along MU (STEP = +1
 // or -1) of the site (xh, c[1], c[2], c[3]) with x = 2 xh + odd, flat index i:
 // along y, z and t the neighbour keeps x and so xh; along x it keeps xh or
@@ -207,7 +198,7 @@ __device__ __forceinline__ void add_staple(M3 &A, Staple &S)
         A = m3_add(A, m3_mul_dag(m3_mul_dag(S.a, S.b), S.c));
     else
         A = m3_add(A, m3_mul(m3_mul(m3_dag(S.a), m3_dag(S.b)), S.c));
-    hb_fence(A);
+    m3_fence(A);
 }
 
 // One Cabibbo-Marinari update of u against staple sum A: for each subgroup
@@ -270,7 +261,7 @@ __device__ void cm_update(M3 &u, const M3 &A, double beta, int mode, int site, i
 // caller's array instead (three rows, the other parity's elements between
 // this one's in every cache line) took 432 us, the parity-split copy with the
 // loads of all six staples issued first (spilled) 200 us, one staple at a
-// time 124 us (three waves per SIMD), the next staple's loads in flight 117
+// time (m3_fence) 124 us (three waves per SIMD), the next staple's loads in flight 117
 // us (two waves per SIMD); blocks not renumbered by XCD 132 us.
 template <bool FULL, int MODE, int MU>
 __global__ __launch_bounds__(kSiteBlock, 2) void k_heatbath(const Cfg *__restrict__ cfgs, int par, double beta,
@@ -453,7 +444,7 @@ __global__ __launch_bounds__(kSiteBlock, 2) void k_plaquette(const Cfg *__restri
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     m[i] = m3_dag_mul(ut, m3_mul(u[i], hb_load<true>(Ut, V, f[i] + ts)));
-                    hb_fence(m[i]);
+                    m3_fence(m[i]);
                 }
             }
             sum = dd_add(sum, dd{acc, 0.0});
@@ -518,10 +509,10 @@ hipError_t launch_heatbath_unpack(const Launch &L, int nblk)
     return hipGetLastError();
 }
 
-hipError_t launch_plaquette(const Launch &L, int nb3, int tch, int Lt, double *out)
+hipError_t launch_plaquette(const Launch &L, const MarchPlan &m, double *out)
 {
-    const int nblk = nb3 * (Lt / tch);
-    hipLaunchKernelGGL(k_plaquette, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs, nb3, tch);
+    const int nblk = m.nb3 * (m.Lt / m.tch);
+    hipLaunchKernelGGL(k_plaquette, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs, m.nb3, m.tch);
     hipLaunchKernelGGL(k_sum_plaquette, dim3(1), dim3(256), 0, L.stream, L.cfgs, nblk, out);
     return hipGetLastError();
 }

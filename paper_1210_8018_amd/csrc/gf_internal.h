@@ -245,12 +245,19 @@ hipError_t launch_touch_links(const Launch &L);
 hipError_t launch_heatbath_sweep(const Launch &L, int V, int mode, int full, double beta, uint64_t seed, long long n);
 hipError_t launch_heatbath_pack(const Launch &L, int nblk);
 hipError_t launch_heatbath_unpack(const Launch &L, int nblk);
-// nb3 site sets of kSiteBlock sites of the (x, y, z) volume, tch t-slices per
-// block (a divisor of Lt); needs 2 nb3 Lt / tch doubles of partials
-hipError_t launch_plaquette(const Launch &L, int nb3, int tch, int Lt, double *out);
+// Walks of the plaquette and of the functional: nb3 sets of kSiteBlock
+// consecutive sites of the (x, y, z) volume, tch t-slices (a divisor of Lt)
+// per block.
+struct MarchPlan {
+    int nb3, tch, Lt;
+};
+hipError_t launch_plaquette(const Launch &L, const MarchPlan &m, double *out);
 hipError_t launch_unpack_links(const Launch &L);
-hipError_t launch_functional_g_impl(const Launch &L, int nblk, const double *omega, double scale, double *out);
-hipError_t launch_functional_g_backward_impl(const Launch &L, int nblk, const double *omega, double scale,
-                                             double *d_omega, double2 *d_U);
+// gf_functional.hip (two doubles of partials per walk block)
+hipError_t launch_functional_g(const Launch &L, int nblk_site, const MarchPlan &m, const double *omega, double scale,
+                               double *out);
+// d_omega or d_U may be null
+hipError_t launch_functional_g_backward(const Launch &L, int nblk_site, const MarchPlan &m, const double *omega,
+                                        double scale, double *d_omega, double2 *d_U);
 
 }  // namespace gfk

@@ -2341,226 +2341,6 @@ __global__ void k_begin_call(const Cfg *__restrict__ cfgs, int ncfg, int in_call
     ct->in_caller = in_caller;
 }
 
-// ============================================================ differentiable functional
-// exp(X) and its Frechet derivative L(X, E) for X = i Q, Q = sum_a w_a lambda_a,
-// by a truncated Taylor series of exp(X / 2^j) coupled with its derivative
-// (d/dt (Y + tE)^k = D_{k-1} Y + Y^{k-1} E), followed by j squarings
-// exp(2Z) = exp(Z)^2, L(2Z, 2F) = L(Z, F) exp(Z) + exp(Z) L(Z, F)
-// (Al-Mohy and Higham, SIAM J. Matrix Anal. Appl. 30, 2009).
-__device__ __forceinline__ M3 algebra_i(const double w[8])
-{
-    // X = i sum_a w_a lambda_a, lambda_a Gell-Mann
-    const double r3 = 0.57735026918962576451;
-    M3 Q = m3_zero();
-    Q.e[1] = make_double2(w[0], -w[1]);
-    Q.e[3] = make_double2(w[0], w[1]);
-    Q.e[0].x = w[2] + w[7] * r3;
-    Q.e[4].x = -w[2] + w[7] * r3;
-    Q.e[8].x = -2.0 * w[7] * r3;
-    Q.e[2] = make_double2(w[3], -w[4]);
-    Q.e[6] = make_double2(w[3], w[4]);
-    Q.e[5] = make_double2(w[5], -w[6]);
-    Q.e[7] = make_double2(w[5], w[6]);
-    M3 X;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) X.e[k] = make_double2(-Q.e[k].y, Q.e[k].x);
-    return X;
-}
-
-__device__ __forceinline__ int scaling_power(const M3 &X)
-{
-    double n = 0.0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) n += cnorm2(X.e[k]);
-    n = sqrt(n);
-    int j = 0;
-    while (n > 0.5 && j < 60) {
-        n *= 0.5;
-        ++j;
-    }
-    return j;
-}
-
-constexpr int kTaylor = 18;
-
-__device__ M3 expm_taylor(const M3 &X)
-{
-    const int j = scaling_power(X);
-    const M3 Y = m3_scale(X, ldexp(1.0, -j));
-    M3 term = m3_identity(), acc = m3_identity();
-    for (int k = 1; k <= kTaylor; ++k) {
-        term = m3_scale(m3_mul(term, Y), 1.0 / (double)k);
-        acc = m3_add(acc, term);
-    }
-    for (int i = 0; i < j; ++i) acc = m3_mul(acc, acc);
-    return acc;
-}
-
-__device__ void expm_frechet_taylor(const M3 &X, const M3 &E, M3 &ex, M3 &Lx)
-{
-    const int j = scaling_power(X);
-    const double sc = ldexp(1.0, -j);
-    const M3 Y = m3_scale(X, sc);
-    const M3 F = m3_scale(E, sc);
-    M3 term = m3_identity(), dterm = m3_zero();
-    M3 acc = m3_identity(), dacc = m3_zero();
-    for (int k = 1; k <= kTaylor; ++k) {
-        const double ik = 1.0 / (double)k;
-        const M3 nd = m3_scale(m3_add(m3_mul(dterm, Y), m3_mul(term, F)), ik);
-        term = m3_scale(m3_mul(term, Y), ik);
-        dterm = nd;
-        acc = m3_add(acc, term);
-        dacc = m3_add(dacc, dterm);
-    }
-    for (int i = 0; i < j; ++i) {
-        dacc = m3_add(m3_mul(dacc, acc), m3_mul(acc, dacc));
-        acc = m3_mul(acc, acc);
-    }
-    ex = acc;
-    Lx = dacc;
-}
-
-__device__ __forceinline__ void load_omega(const double *__restrict__ om, int V, int s, double w[8])
-{
-#pragma unroll
-    for (int a = 0; a < 8; ++a) w[a] = om[(size_t)a * V + s];
-}
-
-// g(x) = exp(i sum_a lambda_a omega_a(x)) into the configuration's g buffer.
-__global__ __launch_bounds__(kSiteBlock) void k_expg(const Cfg *__restrict__ cfgs, const double *__restrict__ omega)
-{
-    const Cfg &C = cfgs[0];
-    const int s = blockIdx.x * kSiteBlock + threadIdx.x;
-    if (s >= C.V) return;
-    double w[8];
-    load_omega(omega, C.V, s, w);
-    m3_store(C.g, C.V, s, expm_taylor(algebra_i(w)));
-}
-
-// Per-block partial sums of sum_mu Re Tr[g(x) U_mu(x) g^dag(x+mu)] (Eq. 1).
-__global__ __launch_bounds__(kSiteBlock) void k_fg_partials(const Cfg *__restrict__ cfgs)
-{
-    __shared__ dd red[2 * (kSiteBlock / 64)];
-    const Cfg &C = cfgs[0];
-    const int V = C.V;
-    const int s = blockIdx.x * kSiteBlock + threadIdx.x;
-    double acc = 0.0;
-    if (s < V) {
-        int x[4];
-        site_coords(C.dims, s, x);
-        const M3 gx = m3_load(C.g, V, s);
-        int stride = 1;
-        for (int mu = 0; mu < 4; ++mu) {
-            const int Lm = C.dims[mu];
-            const int sf = (x[mu] == Lm - 1) ? s - (Lm - 1) * stride : s + stride;
-            stride *= Lm;
-            const M3 u = m3_load(C.U + (size_t)mu * 9 * V, V, s);
-            const M3 gf = m3_load(C.g, V, sf);
-            const M3 w = m3_mul_dag(m3_mul(gx, u), gf);
-            acc += w.e[0].x + w.e[4].x + w.e[8].x;
-        }
-    }
-    dd a = {acc, 0.0}, b = {0.0, 0.0};
-    block_sum2(a, b, red);
-    if (threadIdx.x == 0) {
-        double *p = C.partials + (size_t)blockIdx.x * 4;
-        p[0] = a.hi;
-        p[1] = a.lo;
-        p[2] = 0.0;
-        p[3] = 0.0;
-    }
-}
-
-// Sum of the first partial pair of every block, times `scale`, to *out.
-__global__ __launch_bounds__(256) void k_sum_partials(const Cfg *__restrict__ cfgs, double scale,
-                                                      double *__restrict__ out)
-{
-    __shared__ dd red[2 * (256 / 64)];
-    const Cfg &C = cfgs[0];
-    dd f = {0.0, 0.0}, z = {0.0, 0.0};
-    for (int i = threadIdx.x; i < C.nblk_site; i += blockDim.x) {
-        const double *p = C.partials + (size_t)i * 4;
-        f = dd_add(f, dd{p[0], p[1]});
-    }
-    block_sum2(f, z, red);
-    if (threadIdx.x == 0) *out = (f.hi + f.lo) * scale;
-}
-
-// Gradients of Eq. 1 with g = exp(X), X = i omega.lambda:
-//   dF/domega_a(x) = Re Tr[L(X, i lambda_a) Sigma(x)] / (12 V)
-//                  = Re Tr[i lambda_a L(X, Sigma(x))] / (12 V),
-//   Sigma(x) = sum_mu [U_mu(x) g^dag(x+mu) + U_mu^dag(x-mu) g^dag(x-mu)],
-// using Tr[L(X,E) S] = Tr[E L(X,S)]; and
-//   dF/dRe U_mu(x) + i dF/dIm U_mu(x) = g^dag(x) g(x+mu) / (12 V).
-__global__ __launch_bounds__(kSiteBlock) void k_fg_backward(const Cfg *__restrict__ cfgs,
-                                                            const double *__restrict__ omega, double scale,
-                                                            double *__restrict__ d_omega, double2 *__restrict__ d_U)
-{
-    const Cfg &C = cfgs[0];
-    const int V = C.V;
-    const int s = blockIdx.x * kSiteBlock + threadIdx.x;
-    if (s >= V) return;
-    int x[4];
-    site_coords(C.dims, s, x);
-    const M3 gx = m3_load(C.g, V, s);
-    M3 Sig = m3_zero();
-    int stride = 1;
-    for (int mu = 0; mu < 4; ++mu) {
-        const int Lm = C.dims[mu];
-        const int sf = (x[mu] == Lm - 1) ? s - (Lm - 1) * stride : s + stride;
-        const int sb = (x[mu] == 0) ? s + (Lm - 1) * stride : s - stride;
-        stride *= Lm;
-        const double2 *Um = C.U + (size_t)mu * 9 * V;
-        const M3 gf = m3_load(C.g, V, sf);
-        if (d_omega) {
-            const M3 u = m3_load(Um, V, s);
-            const M3 ub = m3_load(Um, V, sb);
-            const M3 gb = m3_load(C.g, V, sb);
-            Sig = m3_add(Sig, m3_mul_dag(u, gf));
-            // U^dag(x-mu) g^dag(x-mu) = (g(x-mu) U(x-mu))^dag
-            const M3 t = m3_mul(gb, ub);
-            M3 td;
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) td.e[i * 3 + j] = cconj(t.e[j * 3 + i]);
-            Sig = m3_add(Sig, td);
-        }
-        if (d_U) {
-            const M3 dU = m3_scale(m3_dag_mul(gx, gf), scale);
-            m3_store(d_U + (size_t)mu * 9 * V, V, s, dU);
-        }
-    }
-    if (d_omega) {
-        double w[8];
-        load_omega(omega, V, s, w);
-        M3 ex, G;
-        expm_frechet_taylor(algebra_i(w), Sig, ex, G);
-        // Tr[lambda_a G] for the eight Gell-Mann matrices; dF/domega_a = -Im(Tr)/(12V)
-        const double r3 = 0.57735026918962576451;
-        double2 tr[8];
-        tr[0] = cadd(G.e[3], G.e[1]);
-        {
-            const double2 d = csub(G.e[1], G.e[3]);
-            tr[1] = make_double2(-d.y, d.x);
-        }
-        tr[2] = csub(G.e[0], G.e[4]);
-        tr[3] = cadd(G.e[6], G.e[2]);
-        {
-            const double2 d = csub(G.e[2], G.e[6]);
-            tr[4] = make_double2(-d.y, d.x);
-        }
-        tr[5] = cadd(G.e[7], G.e[5]);
-        {
-            const double2 d = csub(G.e[5], G.e[7]);
-            tr[6] = make_double2(-d.y, d.x);
-        }
-        tr[7] = cscale(csub(cadd(G.e[0], G.e[4]), cscale(G.e[8], 2.0)), r3);
-#pragma unroll
-        for (int a = 0; a < 8; ++a) d_omega[(size_t)a * V + s] = -tr[a].y * scale;
-    }
-}
-
 // ============================================================ launchers
 static inline dim3 blocks1(int n, int b) { return dim3((n + b - 1) / b); }
 
@@ -3012,28 +2792,6 @@ hipError_t launch_update(const Launch &L, int respect_done, const double2 *g_ove
 {
     hipLaunchKernelGGL(k_update, dim3(L.total_march_blocks), dim3(kSiteBlock), 0, L.stream, L.cfgs, L.batch,
                        respect_done, g_override, g_override ? 0 : 1);
-    return hipGetLastError();
-}
-
-}  // namespace gfk
-
-// Differentiable functional launchers (single configuration, slot 0).
-namespace gfk {
-
-hipError_t launch_functional_g_impl(const Launch &L, int nblk, const double *omega, double scale, double *out)
-{
-    hipLaunchKernelGGL(k_expg, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs, omega);
-    hipLaunchKernelGGL(k_fg_partials, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, L.stream, L.cfgs, scale, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_functional_g_backward_impl(const Launch &L, int nblk, const double *omega, double scale,
-                                             double *d_omega, double2 *d_U)
-{
-    hipLaunchKernelGGL(k_expg, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs, omega);
-    hipLaunchKernelGGL(k_fg_backward, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs, omega, scale, d_omega,
-                       d_U);
     return hipGetLastError();
 }
 

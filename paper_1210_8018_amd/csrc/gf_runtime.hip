@@ -15,12 +15,6 @@
 #include "../../include/gf.h"
 #include "gf_internal.h"
 
-namespace gfk {
-hipError_t launch_functional_g_impl(const Launch &L, int nblk, const double *omega, double scale, double *out);
-hipError_t launch_functional_g_backward_impl(const Launch &L, int nblk, const double *omega, double scale,
-                                             double *d_omega, double2 *d_U);
-}
-
 using namespace gfk;
 
 namespace {
@@ -136,25 +130,25 @@ int plan_tchunk(const int dims[4], int nb3, bool f64_links, int resident)
     return best;
 }
 
-// t-slices per block of the plaquette kernel: as above, and enough that the
-// blocks' sums (two doubles each) fit the 4 nblk_site doubles of partials
+// Walks of the plaquette and the functional: as above, and long enough that
+// the blocks' sums (two doubles each) fit the 4 nblk_site doubles of partials
 // that every context has.
-int plan_plaquette_tch(const int dims[4], int nb3, int nblk_site, int resident)
+MarchPlan plan_walk(const int dims[4], int nblk_site, int resident)
 {
-    int best = 0;
-    double best_cost = 1e300;
+    MarchPlan m{(dims[0] * dims[1] * dims[2] + kSiteBlock - 1) / kSiteBlock, 0, dims[3]};
+    double best = 1e300;
     for (int t = 1; t <= dims[3]; ++t) {
         if (dims[3] % t) continue;
-        const long long nb = (long long)nb3 * (dims[3] / t);
-        if (nb > 2LL * nblk_site) continue;
-        if (best && t > kMaxTchunk) break;
+        const long long nb = (long long)m.nb3 * (dims[3] / t);
+        if (nb > 2LL * nblk_site) continue;  // t = Lt always fits: nb3 <= nblk_site
+        if (m.tch && t > kMaxTchunk) break;
         const double cost = (double)((nb + resident - 1) / resident) * (t + 0.23);
-        if (!best || cost <= best_cost) {
-            best_cost = cost;
-            best = t;
+        if (!m.tch || cost <= best) {
+            best = cost;
+            m.tch = t;
         }
     }
-    return best;  // at least Lt itself: nb3 <= nblk_site
+    return m;
 }
 
 // In a batch every configuration's marching blocks take about the same
@@ -1827,9 +1821,7 @@ gf_status gf_plaquette(gf_ctx c, double *P)
     if (!c || !P) return GF_ERR_ARG;
     if (c->batch) return GF_ERR_STATE;
     const Cfg &C = c->cfg[0];
-    const int nb3 = (C.V3 + kSiteBlock - 1) / kSiteBlock;
-    const int tch = plan_plaquette_tch(C.dims, nb3, C.nblk_site, kMarchResidentPerCU * c->ncu);
-    HIPCHK(c, launch_plaquette(c->L, nb3, tch, C.dims[3], c->d_scalar));
+    HIPCHK(c, launch_plaquette(c->L, plan_walk(C.dims, C.nblk_site, kMarchResidentPerCU * c->ncu), c->d_scalar));
     double h = 0.0;
     HIPCHK(c, hipMemcpyAsync(&h, c->d_scalar, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1865,7 +1857,8 @@ gf_status gf_functional_g(gf_ctx c, const double *d_omega, double *F)
     if (!c || !d_omega) return GF_ERR_ARG;
     if (c->batch) return GF_ERR_STATE;
     const Cfg &C = c->cfg[0];
-    HIPCHK(c, launch_functional_g_impl(c->L, C.nblk_site, d_omega, 1.0 / (12.0 * (double)C.V), c->d_scalar));
+    const MarchPlan m = plan_walk(C.dims, C.nblk_site, kMarchResidentPerCU * c->ncu);
+    HIPCHK(c, launch_functional_g(c->L, C.nblk_site, m, d_omega, 1.0 / (12.0 * (double)C.V), c->d_scalar));
     double h = 0.0;
     HIPCHK(c, hipMemcpyAsync(&h, c->d_scalar, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1880,8 +1873,9 @@ gf_status gf_functional_g_backward(gf_ctx c, const double *d_omega, double grad_
     if (c->batch) return GF_ERR_STATE;
     const Cfg &C = c->cfg[0];
     if (!d_dF_domega && !d_dF_dU) return GF_OK;
-    HIPCHK(c, launch_functional_g_backward_impl(c->L, C.nblk_site, d_omega, grad_out / (12.0 * (double)C.V),
-                                                d_dF_domega, (double2 *)d_dF_dU));
+    const MarchPlan m = plan_walk(C.dims, C.nblk_site, kMarchResidentPerCU * c->ncu);
+    HIPCHK(c, launch_functional_g_backward(c->L, C.nblk_site, m, d_omega, grad_out / (12.0 * (double)C.V), d_dF_domega,
+                                           (double2 *)d_dF_dU));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return GF_OK;
 }

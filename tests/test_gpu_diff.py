@@ -119,3 +119,29 @@ def test_functional_context_is_light_reused_and_checks_omega():
     for bad in (omd.detach().float(), omd.detach()[:, : V - 1], omd.detach().cpu(), omd.detach().reshape(-1)):
         with pytest.raises(ValueError):
             GaugeFunctional.apply(Ud, bad)
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (3, 4, 6, 2), (9, 8, 4, 27), (16, 12, 6, 8)])
+@pytest.mark.parametrize("sigma", [1e-9, 0.03, 0.6, 6.0])
+def test_walks_and_scalings(dims, sigma):
+    """Less than a site set, ragged and whole sets, one and several slices per
+    walk; no and many squarings of the exponential. Each output alone equals
+    the two together bit for bit. Bounds: those of
+    test_forward_and_backward_match_oracle, times the condition |omega| of the
+    exponential above 1."""
+    V = int(np.prod(dims))
+    U, om = random_links(dims, 0.3, 61), random_omega(dims, sigma, 62)
+    Ud, omd = dev(U), dev(om)
+    fx = GaugeFixer(Ud)
+    cond = max(1.0, 4 * sigma)
+    assert abs(gf.gf_functional_g(fx.ctx, omd) - oracle.functional_g(dims, U, om)) < 1e-14 * cond
+    d_om, d_U = torch.empty_like(omd), torch.empty_like(Ud)
+    gf.gf_functional_g_backward(fx.ctx, omd, 0.7, d_om, d_U)
+    ref = 0.7 * oracle.grad_omega_sites(dims, U, om, np.arange(V)).T
+    assert np.max(np.abs(host(d_om) - ref)) < 1e-13 * cond * np.max(np.abs(ref))
+    refU = 0.7 * oracle.grad_links(dims, om)
+    assert np.max(np.abs(host(d_U).reshape(4, 3, 3, V) - refU)) < 1e-13 * cond / (12 * V)
+    o2, U2 = torch.empty_like(omd), torch.empty_like(Ud)
+    gf.gf_functional_g_backward(fx.ctx, omd, 0.7, o2, None)
+    gf.gf_functional_g_backward(fx.ctx, omd, 0.7, None, U2)
+    assert torch.equal(o2, d_om) and torch.equal(U2, d_U)
