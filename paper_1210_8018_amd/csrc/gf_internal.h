@@ -94,7 +94,7 @@ struct Ctrl {
     long long max_iter;  // absolute cap on iter
     int done;            // kRunning / kConverged / kMaxIter / kNonFinite
     int cur;             // current two-row link buffer, U12[cur]
-    int ru_now;          // this iteration also projects the new links (set before the fused pass)
+    int ru_now;          // the coming iteration also projects the new links
     int in_caller;       // the current links are the caller's array U (full 3x3), not U12[cur]
     int pad2;
     double hist[kHist][2];  // (F, theta) after update k at slot k % kHist
@@ -198,7 +198,6 @@ struct Launch {
     int fp32;             // transform precision
     int fused;            // iterations use the fused update + divergence kernel
     int link_f32;         // links and g held in single-precision two-row storage (this phase)
-    int any_reunit;       // some configuration projects its links every R updates
     int ncfg;
     hipStream_t stream;
 };
@@ -211,10 +210,9 @@ hipError_t launch_reduce(const Launch &L, int ncfg, int count_iter, int respect_
 hipError_t launch_fft_axis(const Launch &L, int axis, int sign, int mode, void *fields_override,
                            int nfields, int respect_done);
 // fold_reduce: the pass also does the final reduction of the previous update
-// (in place of launch_reduce after it); only where can_fold_reduce(L).
+// (in place of launch_reduce after it).
 hipError_t launch_fft_xy(const Launch &L, int sign, void *fields_override, int nfields, int respect_done,
                          int fold_reduce = 0);
-bool can_fold_reduce(const Launch &L);
 hipError_t launch_fft_xy_inv_gauge(const Launch &L, int respect_done, double2 *g_override);
 hipError_t launch_fft_zt(const Launch &L, int mode, int sign, void *fields_override, int nfields, int respect_done);
 hipError_t launch_fft_zt_scale(const Launch &L, int respect_done);
@@ -235,7 +233,9 @@ hipError_t launch_update(const Launch &L, int respect_done, const double2 *g_ove
 // for the first update of a call (old links) or the last of a gf_step call
 // (new links).
 enum : int { kLinksBuffers = 0, kLinksFromCaller = 1, kLinksToCaller = 2 };
-hipError_t launch_update_delta(const Launch &L, int link_io);
+// reunit: some listed configuration projects its links in this update (the
+// instance for those runs too)
+hipError_t launch_update_delta(const Launch &L, int link_io, int reunit);
 hipError_t launch_pack_links(const Launch &L);
 hipError_t launch_momentum_table(const Launch &L);
 // reads every configuration's two-row link buffers (cache eviction before a timed pass)

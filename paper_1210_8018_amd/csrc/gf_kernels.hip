@@ -31,6 +31,7 @@ __global__ void k_arm(const Cfg *__restrict__ cfgs, int ncfg, double eps, long l
     }
     ct->eps = eps;
     ct->max_iter = ct->iter + add_iters;
+    ct->ru_now = next_reunit(cfgs[c], ct->iter);
     int d = kRunning;
     if (!reset) {
         if (!isfinite(ct->F) || !isfinite(ct->theta))
@@ -868,12 +869,10 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(CAP / TH >= 
     extern __shared__ __align__(16) unsigned char smem[];
     const int ntiles = B->off_xy[B->n];
     if ((int)blockIdx.x >= ntiles) {
-        if constexpr (TH >= kReduceLanes) {
-            if (blockIdx.y != 0) return;
-            const Cfg &R = cfgs[B->idx[blockIdx.x - ntiles]];
-            if (R.ctrl->done) return;
-            finalize_config(R, R.nblk_march, 1, fold == 2, (dd *)smem);
-        }
+        if (blockIdx.y != 0) return;
+        const Cfg &R = cfgs[B->idx[blockIdx.x - ntiles]];
+        if (R.ctrl->done) return;
+        finalize_config(R, R.nblk_march, 1, fold == 2, (dd *)smem);
         return;
     }
     const int tile = xcd_remap(blockIdx.x, ntiles);
@@ -2319,16 +2318,6 @@ __global__ __launch_bounds__(kSiteBlock) void k_unpack_links(const Cfg *__restri
     }
 }
 
-// Whether the coming iteration of each running configuration projects its links.
-__global__ void k_mark_reunit(const Cfg *__restrict__ cfgs, const Batch *__restrict__ B)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= B->n) return;
-    const Cfg &C = cfgs[B->idx[e]];
-    Ctrl *ct = C.ctrl;
-    ct->ru_now = C.reunit_every > 0 && ((ct->iter + 1) % (long long)C.reunit_every) == 0;
-}
-
 // Start of an iterating call: links in buffer 0 (binary32 storage, copied by
 // k_pack_links) or in the caller's array (FP64 storage, read there by the
 // first update).
@@ -2461,12 +2450,11 @@ static hipError_t run_xy(const Launch &L, int nf, int sign, void *fo, int rd, in
     if (!fo && L.xy_reg_any) {  // the iteration's forward pass
         if (sign != -1 || nf != kFields) return hipErrorInvalidValue;
         const int ng = L.xy_reg_groups;
-        // one instance per plane size present; the first with at least
-        // kReduceLanes work-items carries the fold
+        // one instance per plane size present; the first carries the fold
 #define GF_XYR(L_)                                                                                               \
     if (L.xy_m & (1 << line_len_bit(L_))) {                                                                      \
-        const int f = xy_reg_threads<L_>() >= kReduceLanes ? fold : 0;                                           \
-        if (f) fold = 0;                                                                                         \
+        const int f = fold;                                                                                      \
+        fold = 0;                                                                                                \
         hipLaunchKernelGGL((k_fft_xy_reg<T2, L_>), dim3(L.total_xy_tiles * ng + (f ? L.ncfg : 0)),               \
                            dim3(xy_reg_threads<L_>()), xy_reg_lds_elems<L_>() * sizeof(T2), L.stream, L.cfgs,     \
                            L.batch, rd, ng, f);                                                                  \
@@ -2590,27 +2578,9 @@ static hipError_t run_xyg(const Launch &L, int rd, double2 *go)
     return launched ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-// The fold needs a work-group of kReduceLanes work-items: a register xy
-// instance of 16-, 32- or 64-point planes (256), or the LDS-staged pass with
-// work-groups that large.
-bool can_fold_reduce(const Launch &L)
-{
-    int big = 0;  // register instances of 256 work-items
-    if (xy_reg_threads<16>() >= kReduceLanes) big |= 1 << line_len_bit(16);
-    if (xy_reg_threads<24>() >= kReduceLanes) big |= 1 << line_len_bit(24);
-    if (xy_reg_threads<32>() >= kReduceLanes) big |= 1 << line_len_bit(32);
-    if (xy_reg_threads<48>() >= kReduceLanes) big |= 1 << line_len_bit(48);
-    if (xy_reg_threads<64>() >= kReduceLanes) big |= 1 << line_len_bit(64);
-    const bool reg = L.xy_reg_any && (L.xy_m & big);
-    const bool lds = (L.xy_p2 || L.xy_gen) && L.xy_th >= kReduceLanes;
-    return reg || lds || L.xy_any_it;
-}
-
 hipError_t launch_fft_xy(const Launch &L, int sign, void *fields_override, int nfields, int respect_done,
                          int fold_reduce)
 {
-    // the folded reduction needs a work-group of at least kReduceLanes
-    if (fold_reduce && !can_fold_reduce(L)) return hipErrorInvalidValue;
     const int fold = fold_reduce ? (L.fused ? 2 : 1) : 0;
     return L.fp32 ? run_xy<float2>(L, nfields, sign, fields_override, respect_done, fold)
                   : run_xy<double2>(L, nfields, sign, fields_override, respect_done, fold);
@@ -2703,16 +2673,15 @@ hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override, 
     return hipGetLastError();
 }
 
-hipError_t launch_update_delta(const Launch &L, int link_io)
+hipError_t launch_update_delta(const Launch &L, int link_io, int reunit)
 {
     const int nb = (L.march_pair == 1 || (L.march_pair == 2 && L.link_f32)) ? 2 : 1;
     const dim3 grid(L.total_march_blocks / nb), blk(kSiteBlock * nb);
-    if (L.any_reunit) hipLaunchKernelGGL(k_mark_reunit, dim3((L.ncfg + 63) / 64), dim3(64), 0, L.stream, L.cfgs, L.batch);
 #define GF_UPD_NB(T2_, S2_, SRC_, DST_, NB_)                                                                       \
     do {                                                                                                           \
         hipLaunchKernelGGL((k_update_delta_x<T2_, false, S2_, SRC_, DST_, NB_>), grid, blk, 0, L.stream, L.cfgs,   \
                            L.batch);                                                                               \
-        if (L.any_reunit)                                                                                          \
+        if (reunit)                                                                                                \
             hipLaunchKernelGGL((k_update_delta_x<T2_, true, S2_, SRC_, DST_, NB_>), grid, blk, 0, L.stream, L.cfgs, \
                                L.batch);                                                                           \
     } while (0)

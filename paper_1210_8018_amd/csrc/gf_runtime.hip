@@ -151,17 +151,6 @@ MarchPlan plan_walk(const int dims[4], int nblk_site, int resident)
     return m;
 }
 
-// In a batch every configuration's marching blocks take about the same
-// number of t-slices (the largest divisor of Lt up to GF_TCHUNK_BATCH,
-// default 4), so blocks carry equal work whatever lattice they belong to and
-// the XCDs, each of which walks a contiguous range of blocks, stay balanced.
-int plan_tchunk_batch(const int dims[4])
-{
-    const char *env = getenv("GF_TCHUNK_BATCH");
-    const int T = env && atoi(env) >= 1 ? atoi(env) : 4;
-    return largest_divisor_at_most(dims[3], T);
-}
-
 // xy tiles: Q consecutive xy-planes, Q * Lx * Ly <= target elements.
 int plan_xyQ(const int dims[4], int target)
 {
@@ -374,8 +363,8 @@ struct gf_ctx_s {
     int ncu = 1;             // compute units of the device
     Ctrl *h_ctrl = nullptr;  // pinned mirror, ncfg entries
     std::vector<std::vector<double>> histF, histT;
-    hipGraphExec_t gexec = nullptr;
-    hipGraph_t graph = nullptr;
+    hipGraphExec_t gexec[2] = {nullptr, nullptr};  // a chunk without / with link projections
+    hipGraph_t graph[2] = {nullptr, nullptr};
     int chunk = kDefaultChunk;
     std::string err;
     bool timing = false;
@@ -385,6 +374,7 @@ struct gf_ctx_s {
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> pending;
     int sched = kSched1D;
     Tiles tiles;
+    bool spread_groups = false;  // plan_groups may split tiles further than `tiles` says
     // a context that allocates nothing (no stream, event, graph or pinned
     // host memory); iterations are launched directly on `stream`
     bool noalloc = false;
@@ -499,10 +489,20 @@ hipError_t enqueue_gauge_steps(gf_ctx c, hipStream_t s, int respect_done, double
 }
 
 // Whether the final reduction of an update can ride on the next iteration's
-// first pass (an xy pass with work-groups of at least 256 work-items).
-bool fold_ok(gf_ctx c)
+// first pass (an xy pass).
+bool fold_ok(gf_ctx c) { return c->sched == kSchedXYZT || c->sched == kSchedXY1D; }
+
+// Whether some configuration of the active map projects its links in one of
+// the n updates after the next `ahead` (counted from the control block last
+// read; a configuration that has stopped since only makes this say yes
+// without need).
+int reunit_within(gf_ctx c, long long ahead, long long n)
 {
-    return (c->sched == kSchedXYZT || c->sched == kSchedXY1D) && can_fold_reduce(c->Lact);
+    for (int k : c->active) {
+        const long long R = c->cfg[k].reunit_every, it = c->h_ctrl[k].iter + ahead;
+        if (R > 0 && (it + n) / R != it / R) return 1;
+    }
+    return 0;
 }
 
 // Alg. 1 inner loop body: transform, scale, transform back, g, link update,
@@ -511,16 +511,18 @@ bool fold_ok(gf_ctx c)
 // iteration's first pass; reduce_after: this iteration's own is launched
 // (else the next iteration folds it).
 // link_io: where the fused pass takes the old links from and puts the new
-// ones (kLinksBuffers inside graphs; see launch_update_delta).
-hipError_t enqueue_iteration(gf_ctx c, hipStream_t s, int fold_prev = 0, int reduce_after = 1,
-                             int link_io = kLinksBuffers)
+// ones (kLinksBuffers inside graphs; see launch_update_delta). reunit: some
+// configuration may project its links in this update (reunit_within); the
+// fused pass's instance for those is left out otherwise (4.6 us a launch at
+// 16^3 x 32, and as much for the launch that marked them).
+hipError_t enqueue_iteration(gf_ctx c, hipStream_t s, int fold_prev, int reduce_after, int link_io, int reunit)
 {
     Launch L = c->Lact;
     L.stream = s;
     hipError_t e = enqueue_gauge_steps(c, s, 1, nullptr, fold_prev);
     if (e != hipSuccess) return e;
     if (L.fused) {
-        GF_TRY(K_UPDATE_DELTA, launch_update_delta(L, link_io));
+        GF_TRY(K_UPDATE_DELTA, launch_update_delta(L, link_io, reunit));
     } else {
         GF_TRY(K_UPDATE, launch_update(L, 1, nullptr));
         GF_TRY(K_DELTA, launch_delta(L, 1, nullptr));
@@ -537,9 +539,11 @@ hipError_t enqueue_measure(gf_ctx c)
     return launch_reduce(c->L, c->ncfg, 0, 0);
 }
 
-gf_status build_graph(gf_ctx c)
+// The graph of a chunk, without (0) or with (1) the instances for updates
+// that project links.
+gf_status build_graph(gf_ctx c, int reunit)
 {
-    if (c->gexec) return GF_OK;
+    if (c->gexec[reunit]) return GF_OK;
     HIPCHK(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
     // inside a chunk each iteration's final reduction rides on the next
@@ -547,7 +551,7 @@ gf_status build_graph(gf_ctx c)
     // so the host reads a complete control block after every chunk
     const bool fold = fold_ok(c);
     for (int i = 0; i < c->chunk && e == hipSuccess; ++i)
-        e = enqueue_iteration(c, c->cap_stream, fold && i > 0, !(fold && i + 1 < c->chunk));
+        e = enqueue_iteration(c, c->cap_stream, fold && i > 0, !(fold && i + 1 < c->chunk), kLinksBuffers, reunit);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(c->cap_stream, &g);
     if (e != hipSuccess) {
@@ -555,8 +559,8 @@ gf_status build_graph(gf_ctx c)
         return fail_hip(c, e, "capture iteration");
     }
     HIPCHK(c, e2);
-    c->graph = g;
-    HIPCHK(c, hipGraphInstantiate(&c->gexec, g, nullptr, nullptr, 0));
+    c->graph[reunit] = g;
+    HIPCHK(c, hipGraphInstantiate(&c->gexec[reunit], g, nullptr, nullptr, 0));
     return GF_OK;
 }
 
@@ -584,10 +588,11 @@ gf_status read_ctrl(gf_ctx c)
     return GF_OK;
 }
 
-gf_status run_chunks(gf_ctx c);
+gf_status run_chunks(gf_ctx c, long long pending);
 gf_status run_exact(gf_ctx c, long long n, long long pending);
 gf_status reset_active(gf_ctx c);
 gf_status compact_active(gf_ctx c);
+gf_status set_active(gf_ctx c, const std::vector<int> &act);
 void drop_graph(gf_ctx c);
 
 // Run graph chunks until every configuration is done. On the fused path the
@@ -616,20 +621,24 @@ gf_status run_until_done(gf_ctx c, long long n_exact = 0)
     if (st != GF_OK) return st;
     if (c->L.fused) HIPCHK(c, launch_pack_links(c->L));
     const bool io = c->L.fused && !c->L.link_f32;
+    // run_exact reads the control block back now and then, so the last update
+    // is placed by the count at the start
+    const int any_reunit = n_exact > 0 ? reunit_within(c, n_exact - 1, 1) : 0;
     long long first = 0;
     if (io) {
-        HIPCHK(c, enqueue_iteration(c, c->stream, 0, 1, kLinksFromCaller));
+        HIPCHK(c, enqueue_iteration(c, c->stream, 0, 1, kLinksFromCaller, reunit_within(c, 0, 1)));
         first = 1;
     }
     if (n_exact > 0) {
         const bool last = io && n_exact >= 2;
         st = run_exact(c, n_exact - first - (last ? 1 : 0), first);
         if (st != GF_OK) return st;
-        if (last) HIPCHK(c, enqueue_iteration(c, c->stream, 0, 1, kLinksToCaller));
+        if (last)
+            HIPCHK(c, enqueue_iteration(c, c->stream, 0, 1, kLinksToCaller, any_reunit));
         if ((st = read_ctrl(c)) != GF_OK) return st;
         if (c->timing && (st = collect_timing(c)) != GF_OK) return st;
     } else {
-        st = run_chunks(c);
+        st = run_chunks(c, first);
         if (st != GF_OK) return st;
     }
     if (c->L.fused) {
@@ -693,28 +702,30 @@ gf_status run_exact(gf_ctx c, long long n, long long pending)
     gf_status st;
     if (c->timing) {
         for (long long i = 0; i < n; ++i) {
-            HIPCHK(c, enqueue_iteration(c, c->stream));
+            HIPCHK(c, enqueue_iteration(c, c->stream, 0, 1, kLinksBuffers, reunit_within(c, i ? 0 : pending, 1)));
             if ((st = read_ctrl(c)) != GF_OK) return st;
             if ((st = collect_timing(c)) != GF_OK) return st;
         }
         return GF_OK;
     }
-    if (n >= c->chunk && (st = build_graph(c)) != GF_OK) return st;
     const bool fold = fold_ok(c);
-    long long left = n, since = pending;
+    long long left = n, since = pending;  // since: updates launched and not read back
     while (left > 0) {
         if (since + c->chunk + 2 > kHist) {
             if ((st = read_ctrl(c)) != GF_OK) return st;
             since = 0;
         }
         if (left >= c->chunk) {
-            HIPCHK(c, hipGraphLaunch(c->gexec, c->stream));
+            const int ru = reunit_within(c, since, c->chunk);
+            if ((st = build_graph(c, ru)) != GF_OK) return st;
+            HIPCHK(c, hipGraphLaunch(c->gexec[ru], c->stream));
             left -= c->chunk;
             since += c->chunk;
         } else {
             const int r = (int)left;
             for (int i = 0; i < r; ++i)
-                HIPCHK(c, enqueue_iteration(c, c->stream, fold && i > 0, !(fold && i + 1 < r)));
+                HIPCHK(c, enqueue_iteration(c, c->stream, fold && i > 0, !(fold && i + 1 < r), kLinksBuffers,
+                                            reunit_within(c, since + i, 1)));
             since += left;
             left = 0;
         }
@@ -723,14 +734,16 @@ gf_status run_exact(gf_ctx c, long long n, long long pending)
 }
 
 // Iterations until every configuration is done (the stopping rule, the cap
-// or a non-finite value), a chunk at a time.
-gf_status run_chunks(gf_ctx c)
+// or a non-finite value), a chunk at a time, after `pending` updates already
+// launched and not yet read back.
+gf_status run_chunks(gf_ctx c, long long pending)
 {
     if (c->timing) {
         // one iteration at a time, every kernel bracketed by events; polling
         // after each iteration means no timed launch is a skipped one
         for (;;) {
-            HIPCHK(c, enqueue_iteration(c, c->stream));
+            HIPCHK(c, enqueue_iteration(c, c->stream, 0, 1, kLinksBuffers, reunit_within(c, pending, 1)));
+            pending = 0;
             gf_status st = read_ctrl(c);
             if (st != GF_OK) return st;
             st = collect_timing(c);
@@ -747,7 +760,9 @@ gf_status run_chunks(gf_ctx c)
         const bool fold = fold_ok(c);
         for (;;) {
             for (int i = 0; i < c->chunk; ++i)
-                HIPCHK(c, enqueue_iteration(c, c->stream, fold && i > 0, !(fold && i + 1 < c->chunk)));
+                HIPCHK(c, enqueue_iteration(c, c->stream, fold && i > 0, !(fold && i + 1 < c->chunk), kLinksBuffers,
+                                            reunit_within(c, pending + i, 1)));
+            pending = 0;
             gf_status st = read_ctrl(c);
             if (st != GF_OK) return st;
             bool all = true;
@@ -755,19 +770,18 @@ gf_status run_chunks(gf_ctx c)
             if (all) return GF_OK;
         }
     }
-    gf_status st = build_graph(c);
-    if (st != GF_OK) return st;
     for (;;) {
-        HIPCHK(c, hipGraphLaunch(c->gexec, c->stream));
+        const int ru = reunit_within(c, pending, c->chunk);
+        gf_status st = build_graph(c, ru);
+        if (st != GF_OK) return st;
+        HIPCHK(c, hipGraphLaunch(c->gexec[ru], c->stream));
+        pending = 0;
         st = read_ctrl(c);
         if (st != GF_OK) return st;
         bool all = true;
         for (int k = 0; k < c->ncfg; ++k) all = all && c->h_ctrl[k].done != kRunning;
         if (all) return GF_OK;
-        if (c->batch) {
-            if ((st = compact_active(c)) != GF_OK) return st;
-            if ((st = build_graph(c)) != GF_OK) return st;
-        }
+        if (c->batch && (st = compact_active(c)) != GF_OK) return st;
     }
 }
 
@@ -897,15 +911,72 @@ void fill_map(gf_ctx c, const std::vector<int> &list, Batch &b, Launch &L)
     }
 }
 
+// In a batch the marching blocks of every listed configuration take about the
+// same number of t-slices (the largest divisor of Lt up to T), so that blocks
+// carry equal work whatever lattice they belong to and the XCDs, each of which
+// walks a contiguous range of blocks, stay balanced. T minimises rounds x (mean
+// walk + 0.23) as in plan_tchunk; GF_TCHUNK_BATCH fixes it. Planned anew when
+// the list shrinks: one 16^3 x 32 lattice left of 16 took 38 us per fused
+// pass with the walks of 4 slices its batch began with, 26 with single ones.
+void plan_batch_walks(gf_ctx c, const std::vector<int> &list)
+{
+    const char *env = getenv("GF_TCHUNK_BATCH");
+    const int fixed = env && atoi(env) >= 1 ? atoi(env) : 0;
+    int best = 1;
+    double best_cost = 1e300;
+    for (int T = 1; T <= 4 && !fixed; ++T) {
+        long long nb = 0;
+        double work = 0.0;
+        for (int k : list) {
+            const Cfg &C = c->cfg[k];
+            const int t = largest_divisor_at_most(C.dims[3], T);
+            const long long n = (long long)C.nb3 * (C.dims[3] / t);
+            nb += n;
+            work += (double)n * (t + 0.23);
+        }
+        const long long res = (long long)kMarchResidentPerCU * c->ncu;
+        const double cost = (double)((nb + res - 1) / res) * work / (double)std::max(1LL, nb);
+        if (cost <= best_cost) {
+            best_cost = cost;
+            best = T;
+        }
+    }
+    for (int k : list) {
+        Cfg &C = c->cfg[k];
+        C.tch = largest_divisor_at_most(C.dims[3], fixed ? fixed : best);
+        C.nblk_march = C.nb3 * (C.dims[3] / C.tch);
+    }
+}
+
+// Work-groups per tile of the register 2D passes (the four fields split among
+// them): the tuned or default number, more while the listed tiles do not give
+// every CU two. The values do not depend on it. 24^4, FP32 transform (144
+// tiles): 113 us per iteration with one (x, y) and two (z, t) work-groups per
+// tile and the reduction launched alone, 102 with four and the reduction on
+// the (x, y) pass; 16^3 x 32 59 and 49.
+void plan_groups(gf_ctx c, const std::vector<int> &list, Launch &L)
+{
+    long long xy = 0, zt = 0;
+    for (int k : list) {
+        if (c->cfg[k].xy_reg) xy += c->cfg[k].nxy;
+        if (c->cfg[k].zt_reg) zt += c->cfg[k].nzt;
+    }
+    const auto spread = [&](int g, long long tiles) {
+        if (g < 1) g = 1;
+        while (c->spread_groups && tiles && g < kFields && tiles * g < 2LL * c->ncu) g *= 2;
+        return g;
+    };
+    L.xy_reg_groups = spread(c->tiles.xy_reg, xy);
+    L.zt_reg_groups = spread(c->tiles.zt_reg, zt);
+}
+
 void drop_graph(gf_ctx c)
 {
-    if (c->gexec) {
-        (void)hipGraphExecDestroy(c->gexec);
-        c->gexec = nullptr;
-    }
-    if (c->graph) {
-        (void)hipGraphDestroy(c->graph);
-        c->graph = nullptr;
+    for (int r = 0; r < 2; ++r) {
+        if (c->gexec[r]) (void)hipGraphExecDestroy(c->gexec[r]);
+        if (c->graph[r]) (void)hipGraphDestroy(c->graph[r]);
+        c->gexec[r] = nullptr;
+        c->graph[r] = nullptr;
     }
 }
 
@@ -981,9 +1052,7 @@ gf_status apply_schedule(gf_ctx c, int sched, const Tiles &tl)
         mz = std::max(mz, C.dims[2]);
         mt = std::max(mt, C.dims[3]);
     }
-    c->L.zt_reg_groups = tl.zt_reg > 0 ? tl.zt_reg : 1;
     c->L.zt_reg_p = tl.zt_reg_p;
-    c->L.xy_reg_groups = tl.xy_reg > 0 ? tl.xy_reg : 1;
     auto cap_for = [](int n) { return n <= 1024 ? 1024 : (n <= 2048 ? 2048 : 4096); };
     c->L.xy_cap = cap_for(xy_max);
     c->L.zt_cap = cap_for(zt_max);
@@ -1002,6 +1071,7 @@ gf_status apply_schedule(gf_ctx c, int sched, const Tiles &tl)
     c->L.zt_tw_total = mz + mt;
     c->sched = sched;
     c->tiles = tl;
+    plan_groups(c, all, c->L);
     // the active map starts as the full one
     c->bact = c->bmap;
     c->Lact = c->L;
@@ -1034,8 +1104,26 @@ gf_status compact_active(gf_ctx c)
     for (int k : c->active) w_map += c->cfg[k].nblk_march;
     if (act.empty() || act == c->active) return GF_OK;
     if (w_act * 5 > w_map * 4) return GF_OK;
+    return set_active(c, act);
+}
+
+// Make `act` the active map: its walks and work-groups planned for what is
+// left, the tables uploaded (the map of all configurations too: its block
+// offsets follow their walks).
+gf_status set_active(gf_ctx c, const std::vector<int> &act)
+{
+    if (c->ncfg > 1) {
+        plan_batch_walks(c, act);
+        std::vector<int> all(c->ncfg);
+        for (int k = 0; k < c->ncfg; ++k) all[k] = k;
+        fill_map(c, all, c->bmap, c->L);
+        HIPCHK(c, hipMemcpyAsync(c->d_batch, &c->bmap, sizeof(Batch), hipMemcpyHostToDevice, c->stream));
+    }
     fill_map(c, act, c->bact, c->Lact);
+    plan_groups(c, act, c->Lact);
     c->active = act;
+    if (c->ncfg > 1)
+        HIPCHK(c, hipMemcpyAsync(c->d_cfgs, c->cfg.data(), sizeof(Cfg) * c->ncfg, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->d_batch_act, &c->bact, sizeof(Batch), hipMemcpyHostToDevice, c->stream));
     drop_graph(c);
     return GF_OK;
@@ -1047,11 +1135,7 @@ gf_status reset_active(gf_ctx c)
     if ((int)c->active.size() == c->ncfg) return GF_OK;
     std::vector<int> all(c->ncfg);
     for (int k = 0; k < c->ncfg; ++k) all[k] = k;
-    fill_map(c, all, c->bact, c->Lact);
-    c->active = all;
-    HIPCHK(c, hipMemcpyAsync(c->d_batch_act, &c->bact, sizeof(Batch), hipMemcpyHostToDevice, c->stream));
-    drop_graph(c);
-    return GF_OK;
+    return set_active(c, all);
 }
 
 bool sched_feasible(gf_ctx c, int sched)
@@ -1146,11 +1230,17 @@ gf_status choose_schedule(gf_ctx c, int requested)
         // no timing without events: the 2D passes wherever they fit
         requested = sched_feasible(c, kSchedXYZT) ? kSchedXYZT : sched_feasible(c, kSchedXY1D) ? kSchedXY1D : kSched1D;
     }
-    if (requested != kSchedAuto) return apply_schedule(c, requested, env_tiles());
+    if (requested != kSchedAuto) {
+        c->spread_groups = !getenv("GF_XY_REG") && !getenv("GF_ZT_REG");
+        return apply_schedule(c, requested, env_tiles());
+    }
+    // a tuned batch splits further once configurations have finished
     const std::string key = tune_key(c);
     for (auto &e : tune_cache())
-        if (e.key == key && sched_feasible(c, e.sched) && valid_tiles(e.tiles))
+        if (e.key == key && sched_feasible(c, e.sched) && valid_tiles(e.tiles)) {
+            c->spread_groups = c->ncfg > 1;
             return apply_schedule(c, e.sched, e.tiles);
+        }
     struct Cand {
         int sched;
         Tiles tiles;
@@ -1287,6 +1377,7 @@ gf_status choose_schedule(gf_ctx c, int requested)
     c->ev_used = 0;
     // the fields were transformed in place: measure again so they hold Delta
     HIPCHK(c, enqueue_measure(c));
+    c->spread_groups = c->ncfg > 1;
     gf_status st = apply_schedule(c, pick.sched, pick.tiles);
     if (st != GF_OK) return st;
     tune_cache().push_back({key, pick.sched, pick.tiles});
@@ -1366,8 +1457,7 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
         C.V3 = C.V2 * p.dims[2];
         C.nblk_site = (C.V + kSiteBlock - 1) / kSiteBlock;
         C.nb3 = plan_tile(p.dims, C.tile, C.ntile);
-        C.tch = (ncfg > 1) ? plan_tchunk_batch(p.dims)
-                           : plan_tchunk(p.dims, C.nb3, p.link_prec == 0, kMarchResidentPerCU * c->ncu);
+        C.tch = plan_tchunk(p.dims, C.nb3, p.link_prec == 0, kMarchResidentPerCU * c->ncu);
         C.nblk_march = C.nb3 * (p.dims[3] / C.tch);
         C.U = (double2 *)links[k];
         C.U12[0] = (double2 *)(c->ws + l.links12a);
@@ -1409,6 +1499,7 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
     {
         std::vector<int> all(ncfg);
         for (int k = 0; k < ncfg; ++k) all[k] = k;
+        if (ncfg > 1) plan_batch_walks(c, all);
         fill_map(c, all, c->bmap, c->L);
     }
     c->L.max_lds_elems = max_lds;
@@ -1418,8 +1509,6 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
     c->L.link_f32 = 0;
     c->link_prec = params[0].link_prec;
     c->refine_theta = params[0].refine_theta > 0.0 ? params[0].refine_theta : 1e-10;
-    c->L.any_reunit = 0;
-    for (int k = 0; k < ncfg; ++k) c->L.any_reunit |= params[k].reunit_every > 0;
     c->L.ncfg = ncfg;
     c->L.stream = c->stream;
 
@@ -1441,7 +1530,7 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
     // the chunk graph of FP64 link storage is captured and instantiated here,
     // not inside the first call that runs a whole chunk (about 0.3 ms, more
     // than an iteration)
-    if (!c->noalloc && c->link_prec == 0) return build_graph(c);
+    if (!c->noalloc && c->link_prec == 0) return build_graph(c, 0);
     return GF_OK;
 }
 
@@ -1883,8 +1972,7 @@ gf_status gf_functional_g_backward(gf_ctx c, const double *d_omega, double grad_
 gf_status gf_destroy(gf_ctx c)
 {
     if (!c) return GF_ERR_ARG;
-    if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
-    if (c->graph) (void)hipGraphDestroy(c->graph);
+    drop_graph(c);
     for (auto e : c->ev_pool) (void)hipEventDestroy(e);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->h_ctrl) {

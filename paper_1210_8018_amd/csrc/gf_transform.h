@@ -15,22 +15,43 @@ namespace gfk {
 // block takes part), F = sum/(12 V) (Eq. 1), theta = sum/(3 V) (Eq. 4); with
 // count_iter, count the update, record the history, flip the link buffer if
 // asked and evaluate the stopping rule theta <= eps.
-// The partial sums are taken kReduceLanes at a time in a fixed order; a
-// larger work-group leaves its other work-items at zero, which adds nothing
-// (dd_add of an exact zero returns its other operand), so every caller forms
-// the same sums bit for bit.
+// The partial sums are taken kReduceLanes at a time in a fixed order, each 64
+// of these lanes by one wave; a work-group of fewer waves takes them in turn,
+// one of more leaves the others idle: every caller forms the same sums bit
+// for bit.
 constexpr int kReduceLanes = 256;
 
+// Whether the iteration after update `it` also projects the links.
+__device__ __forceinline__ int next_reunit(const Cfg &C, long long it)
+{
+    return C.reunit_every > 0 && (it + 1) % (long long)C.reunit_every == 0;
+}
+
+// red: 2 kReduceLanes / 64 entries
 static __device__ __forceinline__ void finalize_config(const Cfg &C, int nparts, int count_iter, int flip, dd *red)
 {
     Ctrl *ct = C.ctrl;
-    dd f = {0.0, 0.0}, t = {0.0, 0.0};
-    for (int i = threadIdx.x; i < nparts && (int)threadIdx.x < kReduceLanes; i += kReduceLanes) {
-        const double *p = C.partials + (size_t)i * 4;
-        f = dd_add(f, dd{p[0], p[1]});
-        t = dd_add(t, dd{p[2], p[3]});
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    for (int w = threadIdx.x >> 6; w < kReduceLanes / 64; w += nw) {
+        dd f = {0.0, 0.0}, t = {0.0, 0.0};
+        for (int i = 64 * w + lane; i < nparts; i += kReduceLanes) {
+            const double *p = C.partials + (size_t)i * 4;
+            f = dd_add(f, dd{p[0], p[1]});
+            t = dd_add(t, dd{p[2], p[3]});
+        }
+        f = wave_sum(f);
+        t = wave_sum(t);
+        if (lane == 0) {
+            red[2 * w] = f;
+            red[2 * w + 1] = t;
+        }
     }
-    block_sum2(f, t, red);
+    __syncthreads();
+    dd f = red[0], t = red[1];
+    for (int k = 1; k < kReduceLanes / 64; ++k) {
+        f = dd_add(f, red[2 * k]);
+        t = dd_add(t, red[2 * k + 1]);
+    }
     if (threadIdx.x == 0) {
         const double F = (f.hi + f.lo) / (12.0 * (double)C.V);
         const double th = (t.hi + t.lo) / (3.0 * (double)C.V);
@@ -41,6 +62,7 @@ static __device__ __forceinline__ void finalize_config(const Cfg &C, int nparts,
             it += 1;
             ct->iter = it;
             if (flip) ct->cur ^= 1;
+            ct->ru_now = next_reunit(C, it);
         }
         ct->hist[it % kHist][0] = F;
         ct->hist[it % kHist][1] = th;

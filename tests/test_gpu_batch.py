@@ -120,3 +120,25 @@ def test_single_precision_batch_refines_members_that_reached_refine_theta(monkey
         assert its[k] == it and Fs[k] == F and ths[k] == th, (k, its[k], it, ths[k], th)
         assert np.array_equal(host(Ubs[k]), Uf)
     assert ths[0] <= EPS and ths[2] <= EPS and its[1] == cap
+
+
+def test_walks_replanned_as_members_finish():
+    """Members finish at very different counts, so the walk lengths of those
+    left (and the block offsets of every map) are planned anew in between.
+    Measurements and a second call after that equal those of contexts of one
+    member each, bit for bit; projections every third update included."""
+    members = [((16, 16, 16, 32), 0.25, 301), ((12, 12, 12, 12), 0.02, 302), ((16, 16, 16, 32), 0.02, 303),
+               ((8, 8, 8, 16), 0.3, 304), ((24, 24, 12, 8), 0.02, 305)]
+    links = [random_links(d, e, s) for d, e, s in members]
+    kw = dict(fft_prec=1, fft_schedule=3, reunit_every=3)
+    bl, sl = [dev(u) for u in links], [dev(u) for u in links]
+    bx, fx = BatchGaugeFixer(bl, **kw), [GaugeFixer(u, **kw) for u in sl]
+    for eps in (1e-9, EPS):
+        its, Fs, ths = bx.fix_until(eps, 400)
+        one = [f.fix_until(eps, 400) for f in fx]
+        assert its == [o[0] for o in one]
+        assert all(torch.equal(a, b) for a, b in zip(bl, sl))
+        Fm, tm = bx.functional()
+        for k, f in enumerate(fx):
+            F1, t1 = f.functional()
+            assert abs(Fm[k] - F1) <= 1e-15 * abs(F1) and abs(tm[k] - t1) <= 1e-12 * t1
