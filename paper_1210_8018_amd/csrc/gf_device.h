@@ -526,6 +526,9 @@ __device__ __forceinline__ bool march_xyz(const Cfg &C, int b3, int tid, int &x,
     return iz < C.tile[2] && x < Lx && y < Ly && z < Lz;
 }
 
+// First t-slice of walk tc of the marching kernels.
+__device__ __forceinline__ int walk_start(const Cfg &C, int tc) { return (int)((unsigned)(tc * C.dims[3]) / (unsigned)C.nch); }
+
 struct Site {
     int s;
     int c[4];

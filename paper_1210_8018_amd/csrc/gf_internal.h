@@ -119,8 +119,8 @@ struct Cfg {
     int nb3;              // blocks over the (x, y, z) volume
     int tile[3];          // (x, y, z) extent of one block's sites; tile[0] = 0: kSiteBlock consecutive sites
     int ntile[3];         // tiles along x, y, z (tile mode)
-    int tch;              // t-slices marched by one block
-    int nblk_march;       // nb3 * (Lt / tch): blocks of the marching kernels
+    int nch;              // walks along t: block tc of a site set takes slices [tc Lt / nch, (tc + 1) Lt / nch)
+    int nblk_march;       // nb3 * nch: blocks of the marching kernels
     GF_GLOBAL double2 *U;        // links [4][3][3][V] (the caller's array)
     GF_GLOBAL double2 *U12[2];   // two-row links [4][2][3][V], two buffers (workspace)
     GF_GLOBAL float2 *U12f[2];   // the same two link buffers in single-precision storage (link_prec 1)

@@ -51,7 +51,7 @@ __global__ void k_arm(const Cfg *__restrict__ cfgs, int ncfg, double eps, long l
 // the traceless anti-hermitian Delta, and per-block compensated partial sums
 // of sum_mu Re Tr U_mu(x) (Eq. 1 at g = 1) and |Delta|^2 (Eq. 4).
 // A block owns a set of (x, y, z) sites (kSiteBlock consecutive ones, or a
-// box; see march_xyz) and walks `tch` consecutive t-slices; U_t(x - t) of
+// box; see march_xyz) and walks some consecutive t-slices (walk_start); U_t(x - t) of
 // each slice is the U_t(x) loaded for the previous slice, kept in registers.
 template <typename T2>
 __global__ __launch_bounds__(kSiteBlock) void k_delta(const Cfg *__restrict__ cfgs, const Batch *__restrict__ B,
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kSiteBlock) void k_delta(const Cfg *__restrict__ cf
         back3[0] = (x == 0) ? s3 + (Lx - 1) : s3 - 1;
         back3[1] = (y == 0) ? s3 + (Ly - 1) * Lx : s3 - Lx;
         back3[2] = (z == 0) ? s3 + (Lz - 1) * C.V2 : s3 - C.V2;
-        const int t0 = tc * C.tch;
+        const int t0 = walk_start(C, tc), t1 = walk_start(C, tc + 1);
         const double2 *__restrict__ Ub = C.U;
         const double2 *__restrict__ Ut = Ub + (size_t)27 * V;
         double2 prev[9];
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kSiteBlock) void k_delta(const Cfg *__restrict__ cf
             for (int k = 0; k < 9; ++k) prev[k] = Ut[(size_t)k * V + sp];
         }
         T2 *__restrict__ f = (T2 *)C.fields;
-        for (int t = t0; t < t0 + C.tch; ++t) {
+        for (int t = t0; t < t1; ++t) {
             const int s = s3 + V3 * t;
             double2 D[9];
             double fsum = 0.0;
@@ -1882,7 +1882,7 @@ __global__ __launch_bounds__(TH) void k_fft_xy_inv_gauge(const Cfg *__restrict__
 // ============================================================ S5: link update
 // U_mu(x) -> g(x) U_mu(x) g^dag(x + mu) for the four links of each site; all
 // g were formed before this launch (the two separate loops of Alg. 1). A block
-// owns a set of (x, y, z) sites (see march_xyz) and walks `tch` t-slices:
+// owns a set of (x, y, z) sites (see march_xyz) and walks some t-slices:
 // g(x + t) of one slice is g(x) of the next, kept in registers.
 __global__ __launch_bounds__(kSiteBlock) void k_update(const Cfg *__restrict__ cfgs, const Batch *__restrict__ B,
                                                        int respect_done, const double2 *__restrict__ g_override,
@@ -1906,9 +1906,9 @@ __global__ __launch_bounds__(kSiteBlock) void k_update(const Cfg *__restrict__ c
     fwd3[0] = (x == Lx - 1) ? s3 - (Lx - 1) : s3 + 1;
     fwd3[1] = (y == Ly - 1) ? s3 - (Ly - 1) * Lx : s3 + Lx;
     fwd3[2] = (z == Lz - 1) ? s3 - (Lz - 1) * C.V2 : s3 + C.V2;
-    const int t0 = tc * C.tch;
+    const int t0 = walk_start(C, tc), t1 = walk_start(C, tc + 1);
     M3 gx = m3_load(G, V, s3 + V3 * t0);
-    for (int t = t0; t < t0 + C.tch; ++t) {
+    for (int t = t0; t < t1; ++t) {
         const int s = s3 + V3 * t;
         const int tn = (t + 1 == Lt) ? 0 : t + 1;
         const M3 gn = m3_load(G, V, s3 + V3 * tn);
@@ -2092,7 +2092,7 @@ __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *_
     sf[1] = inside ? block_slot<NB>(C, b3f, fwd3[1], x, yf, z) : -1;
     sb[0] = inside ? block_slot<NB>(C, b3f, back3[0], xb, y, z) : -1;
     sb[1] = inside ? block_slot<NB>(C, b3f, back3[1], x, yb, z) : -1;
-    const int t0 = tc * C.tch;
+    const int t0 = walk_start(C, tc), t1 = walk_start(C, tc + 1);
     dd fs = {0.0, 0.0}, ts = {0.0, 0.0};
     // Slice t forms g(x, t) and completes the site (x, t - 1): its forward
     // t-link needs g(x, t), so it is formed one slice late, and the slice's
@@ -2106,7 +2106,7 @@ __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *_
     AH utp;  // U'_t(x, t - 1) - h.c., the backward t-link of (x, t)
     if (inside) gp = fused_gauge<T2, S2>(C, s3 + V3 * ((t0 == 0) ? Lt - 1 : t0 - 1));
     T2 *__restrict__ f = (T2 *)C.fields;
-    for (int t = t0; t <= t0 + C.tch; ++t) {
+    for (int t = t0; t <= t1; ++t) {
         const int s = s3 + V3 * ((t == Lt) ? 0 : t);
         const int sp = s3 + V3 * ((t == 0) ? Lt - 1 : t - 1);
         M3 gx;
@@ -2145,7 +2145,7 @@ __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *_
                 ts = dd_add(ts, dd{tsum, 0.0});
             }
         }
-        if (t == t0 + C.tch) {  // the walk's last slice: (x, t) belongs to the next block in t
+        if (t == t1) {  // the walk's last slice: (x, t) belongs to the next block in t
             if (inside) fs = dd_add(fs, dd{fsum, 0.0});
             break;
         }

@@ -92,43 +92,55 @@ int plan_tile(const int dims[4], int tile[3], int ntile[3])
     return (dims[0] * dims[1] * dims[2] + kSiteBlock - 1) / kSiteBlock;
 }
 
-// Blocks of the t-marching kernels: nb3 site sets times `tch` t-slices, a
-// walk of at most 8 slices. Each walk re-reads its first slice's
-// t-neighbours (about 0.23 of a slice's traffic); the blocks run in rounds
-// of `resident` (two per CU). The walk length taken minimises
-//   rounds * (tch + 0.23) * (1.05 if a single round, FP64 link storage),
-// largest tch on ties: a single round leaves the CUs idle while its slowest
-// blocks finish, and with FP64 links that costs more than the walk-end
-// re-reads a second round adds. Measured picks (FP64 fused pass): 32^4 4
-// slices (1024 blocks; 8 slices, one round, 2 % slower; binary32 storage
-// the other way round, 8 slices 3 % faster); 24^4 3 slices (432 blocks, one
-// round: 72 us against 77 for 1 slice and 82 for 4); 16^3 x 32 1 slice (512
-// blocks; 2 slices 4 % slower); 48^4 6 slices (3456 blocks; 8 and 4 slices
-// 7 % and 5 % slower); 64^4 8 slices (8192 blocks; one walk over all 64
-// slices 2.7 % slower).
+// Walks of the t-marching kernels: every one of the nb3 site sets takes its Lt
+// slices in nch walks of at most 8, equal or differing by one slice. Each walk
+// re-reads its first slice's t-neighbours (about 0.23 of a slice's traffic);
+// the blocks run in rounds of `resident` (two per CU), nearly in step, so a
+// round lasts as long as its longest walk. The number taken minimises
+//   rounds * (longest walk + 0.23) * (1.05 if a single round, FP64 links),
+// longest walks on ties, unequal ones only where they gain 2 %: a single round
+// leaves the CUs idle while its slowest blocks finish, and with FP64 links
+// that costs more than the walk-end re-reads a second round adds. Measured
+// picks (FP64 fused pass): 32^4 4 slices (1024 blocks; 8 slices, one round,
+// 2 % slower; binary32 storage the other way round, 8 slices 3 % faster);
+// 24^4 3 slices (432 blocks, one round: 72 us against 81 for 1 slice and 81
+// for 4); 16^3 x 32 1 slice (512 blocks; 2 slices 4 % slower); 48^4 6 slices
+// (3456 blocks; 8 and 4 slices 7 % and 5 % slower); 64^4 8 slices (8192
+// blocks; one walk over all 64 slices 2.7 % slower); 36 x 18 x 24 x 54 8 walks
+// of 6 or 7 slices (488 blocks, one round: 161 us against 171 for 1 slice, 172
+// for 2, 175 for 3, and 202 for 9 walks, 37 blocks into a second round).
 constexpr int kMaxTchunk = 8;
-int plan_tchunk(const int dims[4], int nb3, bool f64_links, int resident)
+int plan_walks(const int dims[4], int nb3, bool f64_links, int resident)
 {
+    const int Lt = dims[3];
     const char *env = getenv("GF_TCHUNK");
     if (env) {
         const int t = atoi(env);
-        if (t >= 1 && dims[3] % t == 0) return t;
+        if (t >= 1 && Lt % t == 0) return Lt / t;
     }
-    int best = 1;
+    int best = Lt;
     double best_cost = 1e300;
-    for (int t = 1; t <= kMaxTchunk && t <= dims[3]; ++t) {
-        if (dims[3] % t) continue;
-        const long long nb = (long long)nb3 * (dims[3] / t);
-        const long long rounds = (nb + resident - 1) / resident;
-        double cost = (double)rounds * (t + 0.23);
-        if (rounds == 1 && f64_links) cost *= 1.05;
-        if (cost <= best_cost) {
-            best_cost = cost;
-            best = t;
+    for (int equal = 1; equal >= 0; --equal)
+        for (int n = Lt; n >= 1; --n) {
+            const int len = (Lt + n - 1) / n;
+            if (len > kMaxTchunk) break;
+            if ((Lt % n == 0) != (equal == 1)) continue;
+            const long long nb = (long long)nb3 * n;
+            const long long rounds = (nb + resident - 1) / resident;
+            double cost = (double)rounds * (len + 0.23);
+            if (rounds == 1 && f64_links) cost *= 1.05;
+            if (equal ? cost <= best_cost : cost < 0.98 * best_cost) {
+                best_cost = cost;
+                best = n;
+            }
         }
-    }
     return best;
 }
+
+// Whether the fused pass gains from two site sets per block: a set of
+// kSiteBlock consecutive sites is fewer than 8 whole x-rows, or not whole ones
+// (see fill_map).
+bool wants_pair(const int dims[4]) { return kSiteBlock % dims[0] != 0 || kSiteBlock / dims[0] < 8; }
 
 // Walks of the plaquette and the functional: as above, and long enough that
 // the blocks' sums (two doubles each) fit the 4 nblk_site doubles of partials
@@ -860,9 +872,11 @@ void fill_map(gf_ctx c, const std::vector<int> &list, Batch &b, Launch &L)
         for (int e = 0; e < b.n && can; ++e) {
             const Cfg &C = c->cfg[list[e]];
             can = C.tile[0] == 0 && C.nb3 % 2 == 0;
-            want = want && (kSiteBlock % C.dims[0] != 0 || kSiteBlock / C.dims[0] < 8);
+            want = want && wants_pair(C.dims);
         }
-        L.march_pair = !can ? 0 : (force == 1 || want) ? 1 : 2;
+        // pairs need blocks for most CUs (18^4 in 184 blocks: 43 us, in pairs 54)
+        const bool enough = 2LL * b.off_march[b.n] >= 3LL * c->ncu;
+        L.march_pair = !can ? 0 : force == 1 ? 1 : !enough ? 0 : want ? 1 : 2;
     }
     for (int mu = 0; mu < 4; ++mu) L.total_fft_tiles[mu] = b.off_fft[mu][b.n];
     L.total_xy_tiles = b.off_xy[b.n];
@@ -915,7 +929,7 @@ void fill_map(gf_ctx c, const std::vector<int> &list, Batch &b, Launch &L)
 // same number of t-slices (the largest divisor of Lt up to T), so that blocks
 // carry equal work whatever lattice they belong to and the XCDs, each of which
 // walks a contiguous range of blocks, stay balanced. T minimises rounds x (mean
-// walk + 0.23) as in plan_tchunk; GF_TCHUNK_BATCH fixes it. Planned anew when
+// walk + 0.23) as in plan_walks; GF_TCHUNK_BATCH fixes it. Planned anew when
 // the list shrinks: one 16^3 x 32 lattice left of 16 took 38 us per fused
 // pass with the walks of 4 slices its batch began with, 26 with single ones.
 void plan_batch_walks(gf_ctx c, const std::vector<int> &list)
@@ -943,8 +957,8 @@ void plan_batch_walks(gf_ctx c, const std::vector<int> &list)
     }
     for (int k : list) {
         Cfg &C = c->cfg[k];
-        C.tch = largest_divisor_at_most(C.dims[3], fixed ? fixed : best);
-        C.nblk_march = C.nb3 * (C.dims[3] / C.tch);
+        C.nch = C.dims[3] / largest_divisor_at_most(C.dims[3], fixed ? fixed : best);
+        C.nblk_march = C.nb3 * C.nch;
     }
 }
 
@@ -1457,8 +1471,15 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
         C.V3 = C.V2 * p.dims[2];
         C.nblk_site = (C.V + kSiteBlock - 1) / kSiteBlock;
         C.nb3 = plan_tile(p.dims, C.tile, C.ntile);
-        C.tch = plan_tchunk(p.dims, C.nb3, p.link_prec == 0, kMarchResidentPerCU * c->ncu);
-        C.nblk_march = C.nb3 * (p.dims[3] / C.tch);
+        C.nch = plan_walks(p.dims, C.nb3, p.link_prec == 0, kMarchResidentPerCU * c->ncu);
+        // an empty site set where an odd number would keep the fused pass
+        // from pairing them, where the blocks run in one round (36 x 18 x 24 x
+        // 54, 61 sets: 161 -> 157 us; 36^4, 183 sets in 7 rounds, would go from
+        // 327 to 332) and the partial sums hold them
+        if (ncfg == 1 && C.tile[0] == 0 && C.nb3 % 2 && C.nb3 >= 32 && wants_pair(p.dims) &&
+            (C.nb3 + 1) * C.nch <= kMarchResidentPerCU * c->ncu && (C.nb3 + 1) * C.nch <= C.nb3 * p.dims[3])
+            C.nb3 += 1;
+        C.nblk_march = C.nb3 * C.nch;
         C.U = (double2 *)links[k];
         C.U12[0] = (double2 *)(c->ws + l.links12a);
         C.U12[1] = (double2 *)(c->ws + l.links12b);
