@@ -229,14 +229,16 @@ hipError_t set_lds_limits_any();
 hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override, int from2 = 0);
 hipError_t launch_update(const Launch &L, int respect_done, const double2 *g_override);
 // Where the fused pass of an update takes the old links from and puts the
-// new ones (FP64 link storage): the two-row buffers, or the caller's array
+// new ones: the two-row buffers, or the caller's array
 // for the first update of a call (old links) or the last of a gf_step call
 // (new links).
 enum : int { kLinksBuffers = 0, kLinksFromCaller = 1, kLinksToCaller = 2 };
 // reunit: some listed configuration projects its links in this update (the
 // instance for those runs too)
 hipError_t launch_update_delta(const Launch &L, int link_io, int reunit);
-hipError_t launch_pack_links(const Launch &L);
+// in_caller: the first update reads the caller's links; else they are copied
+// to binary32 two-row buffer 0
+hipError_t launch_begin_call(const Launch &L, int in_caller);
 hipError_t launch_momentum_table(const Launch &L);
 // reads every configuration's two-row link buffers (cache eviction before a timed pass)
 hipError_t launch_touch_links(const Launch &L);

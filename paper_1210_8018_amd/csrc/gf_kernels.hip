@@ -2020,31 +2020,69 @@ __device__ __forceinline__ M3 fused_gauge(const Cfg &C, int s)
         return gauge_at<T2, S2>((const T2 *)C.fields2, C.V, s);
 }
 
-// A new link of the fused pass: rows 0 and 1 in two-row storage S2, or, with
-// FULL (FP64 storage only), all three rows in the layout of the caller's array
-// (row 2 as the two-row form rebuilds it on load: w's own row 2, see m3_row2).
-template <typename S2, bool FULL>
-__device__ __forceinline__ void store_new_link(S2 *__restrict__ base, int V, int s, const M3 &w)
+// An old link of the fused pass from two-row storage S2, or (SRC) from the
+// caller's full matrices: rows 0 and 1 rounded to S2 (no-op for double2), what
+// a two-row copy of them would hold.
+template <typename S2, bool SRC, bool STREAM>
+__device__ __forceinline__ M3 load_old_link(const std::conditional_t<SRC, double2, S2> *__restrict__ base, int V, int s)
 {
-    m3_store12s_stream(base, V, s, w);
-    if constexpr (FULL) {
+    if constexpr (SRC && std::is_same<S2, float2>::value) {
+        M3 m;
 #pragma unroll
-        for (int k = 6; k < 9; ++k) st_stream(base + (size_t)k * V + s, w.e[k]);
+        for (int k = 0; k < 6; ++k) {
+            const double2 *p = base + (size_t)k * V + s;
+            float2 v;
+            narrow(v, STREAM ? ld_stream(p) : *p);
+            m.e[k] = widen(v);
+        }
+        m3_row2(m);
+        return m;
+    } else {
+        return STREAM ? m3_load12s_stream(base, V, s) : m3_load12s(base, V, s);
+    }
+}
+
+// A new link of the fused pass: rows 0 and 1 in two-row storage S2, or, with
+// DST, all three rows in the layout of the caller's array as the two-row form
+// reads back: rows 0 and 1 rounded to S2, row 2 rebuilt from them (for FP64
+// storage w's own row 2, see m3_row2).
+template <typename S2, bool DST>
+__device__ __forceinline__ void store_new_link(std::conditional_t<DST, double2, S2> *__restrict__ base, int V, int s,
+                                               const M3 &w)
+{
+    if constexpr (DST && std::is_same<S2, float2>::value) {
+        M3 m;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            float2 v;
+            narrow(v, w.e[k]);
+            m.e[k] = widen(v);
+        }
+        m3_row2(m);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) st_stream(base + (size_t)k * V + s, m.e[k]);
+    } else {
+        m3_store12s_stream(base, V, s, w);
+        if constexpr (DST) {
+#pragma unroll
+            for (int k = 6; k < 9; ++k) st_stream(base + (size_t)k * V + s, w.e[k]);
+        }
     }
 }
 
 // S2: storage of links and g, double2 or float2 (single-precision storage).
-// SRC / DST (FP64 storage): the first update of a call reads the old links
-// from the caller's array, the last update of a gf_step call writes the new
-// ones there, so that a call copies no links in or out; the updates in
-// between use the two-row buffers (these instances run inside the graphs).
+// SRC / DST: the first update of a call (with binary32 storage: of a gf_step
+// call) reads the old links from the caller's array, the last update of a
+// gf_step call writes the new ones there, so that a call copies no links in or
+// out (32^4, binary32 storage: 150 us to pack and 151 to unpack them, 102 us
+// more in the two updates); the updates in between use the two-row buffers
+// (these instances run inside the graphs).
 // NB: site sets per block (1, or 2 for linear sets: the neighbour exchange
 // spans both, each set keeps its own partial sums).
 template <typename T2, bool RU, typename S2, bool SRC = false, bool DST = false, int NB = 1>
 __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *__restrict__ cfgs,
                                                                     const Batch *__restrict__ B)
 {
-    static_assert(!(SRC || DST) || std::is_same<S2, double2>::value, "caller layout: FP64 storage only");
     constexpr int NS = kSiteBlock * NB;
     __shared__ dd red[2 * (NS / 64)];
     __shared__ double2 sg[6][NS];    // g(x), rows 0 and 1, of the block's sites at this slice
@@ -2062,8 +2100,16 @@ __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *_
     // to the caller's array as full matrices. Per direction, element k of a
     // link sits at base + k V + s in both layouts.
     constexpr size_t kOs = SRC ? 9 : 6, kNs = DST ? 9 : 6;
-    const S2 *__restrict__ Uo = SRC ? (const S2 *)C.U : links12<S2>(C, ct->cur);
-    S2 *__restrict__ Un = DST ? (S2 *)C.U : links12<S2>(C, ct->cur ^ 1);
+    const std::conditional_t<SRC, double2, S2> *__restrict__ Uo;
+    std::conditional_t<DST, double2, S2> *__restrict__ Un;
+    if constexpr (SRC)
+        Uo = C.U;
+    else
+        Uo = links12<S2>(C, ct->cur);
+    if constexpr (DST)
+        Un = C.U;
+    else
+        Un = links12<S2>(C, ct->cur ^ 1);
     const bool reunit = C.reunit_every > 0 && ct->ru_now;
     if (reunit != RU) return;
     const int tid = threadIdx.x;
@@ -2115,7 +2161,8 @@ __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *_
             gx = fused_gauge<T2, S2>(C, s);
             // U'_t(x, t - 1); at the walk's first slice the owner of (x, t0 - 1)
             // stores it, this block only needs its anti-hermitian part
-            const M3 u = (t == t0) ? m3_load12s(Uo + kOs * 3 * V, V, sp) : m3_load12s_stream(Uo + kOs * 3 * V, V, sp);
+            const M3 u = (t == t0) ? load_old_link<S2, SRC, false>(Uo + kOs * 3 * V, V, sp)
+                                   : load_old_link<S2, SRC, true>(Uo + kOs * 3 * V, V, sp);
             M3 w = m3_mul_mul_dag_rows(gp, u, gx);
             if (RU) m3_reunit(w);
             utp = ah_of(w);
@@ -2157,7 +2204,7 @@ __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *_
                 // U_z(x) is the backward neighbour of the next work-group in z,
                 // which reads it in the same slice
                 const M3 gf = fused_gauge<T2, S2>(C, fwd3[2] + V3 * t);
-                M3 w = m3_mul_mul_dag_rows(gx, m3_load12s(Uo + (size_t)2 * kOs * V, V, s), gf);
+                M3 w = m3_mul_mul_dag_rows(gx, load_old_link<S2, SRC, false>(Uo + (size_t)2 * kOs * V, V, s), gf);
                 if (RU) m3_reunit(w);
                 store_new_link<S2, DST>(Un + (size_t)2 * kNs * V, V, s, w);
                 fsum += w.e[0].x + w.e[4].x + w.e[8].x;
@@ -2165,7 +2212,7 @@ __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *_
             }
             {
                 const int sbk = back3[2] + V3 * t;
-                M3 wb = m3_mul_mul_dag_rows(fused_gauge<T2, S2>(C, sbk), m3_load12s(Uo + (size_t)2 * kOs * V, V, sbk), gx);
+                M3 wb = m3_mul_mul_dag_rows(fused_gauge<T2, S2>(C, sbk), load_old_link<S2, SRC, false>(Uo + (size_t)2 * kOs * V, V, sbk), gx);
                 if (RU) m3_reunit(wb);
                 ah_acc(dc, ah_of(wb), 1.0);
             }
@@ -2185,7 +2232,7 @@ __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *_
                     gf = fused_gauge<T2, S2>(C, fwd3[mu] + V3 * t);
                 }
                 // U_x(x) and U_y(x) are read again only at the block's edge rows
-                const M3 u = m3_load12s_stream(Uo + (size_t)mu * kOs * V, V, s);
+                const M3 u = load_old_link<S2, SRC, true>(Uo + (size_t)mu * kOs * V, V, s);
                 M3 w = m3_mul_mul_dag_rows(gx, u, gf);
                 if (RU) m3_reunit(w);
                 store_new_link<S2, DST>(Un + (size_t)mu * kNs * V, V, s, w);
@@ -2219,7 +2266,7 @@ __global__ __launch_bounds__(kSiteBlock * NB) void k_update_delta_x(const Cfg *_
                     a.d2 = sa[nu][8][o];
                 } else {
                     const int sbk = back3[nu] + V3 * t;
-                    M3 wb = m3_mul_mul_dag_rows(fused_gauge<T2, S2>(C, sbk), m3_load12s(Uo + (size_t)nu * kOs * V, V, sbk), gx);
+                    M3 wb = m3_mul_mul_dag_rows(fused_gauge<T2, S2>(C, sbk), load_old_link<S2, SRC, false>(Uo + (size_t)nu * kOs * V, V, sbk), gx);
                     if (RU) m3_reunit(wb);
                     a = ah_of(wb);
                 }
@@ -2318,9 +2365,8 @@ __global__ __launch_bounds__(kSiteBlock) void k_unpack_links(const Cfg *__restri
     }
 }
 
-// Start of an iterating call: links in buffer 0 (binary32 storage, copied by
-// k_pack_links) or in the caller's array (FP64 storage, read there by the
-// first update).
+// Start of an iterating call: links in buffer 0 (copied by k_pack_links) or in
+// the caller's array (read there by the first update).
 __global__ void k_begin_call(const Cfg *__restrict__ cfgs, int ncfg, int in_caller)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
@@ -2692,26 +2738,25 @@ hipError_t launch_update_delta(const Launch &L, int link_io, int reunit)
         else                                       \
             GF_UPD_NB(T2_, S2_, SRC_, DST_, 1);    \
     } while (0)
-#define GF_UPD_IO(T2_)                                    \
+#define GF_UPD_IO(T2_, S2_)                               \
     do {                                                  \
         if (link_io == kLinksFromCaller)                  \
-            GF_UPD(T2_, double2, true, false);            \
+            GF_UPD(T2_, S2_, true, false);            \
         else if (link_io == kLinksToCaller)               \
-            GF_UPD(T2_, double2, false, true);            \
+            GF_UPD(T2_, S2_, false, true);            \
         else                                              \
-            GF_UPD(T2_, double2, false, false);           \
+            GF_UPD(T2_, S2_, false, false);           \
     } while (0)
-    if (L.link_f32 && link_io != kLinksBuffers) return hipErrorInvalidValue;
     if (L.fp32) {
         if (L.link_f32)
-            GF_UPD(float2, float2, false, false);
+            GF_UPD_IO(float2, float2);
         else
-            GF_UPD_IO(float2);
+            GF_UPD_IO(float2, double2);
     } else {
         if (L.link_f32)
-            GF_UPD(double2, float2, false, false);
+            GF_UPD_IO(double2, float2);
         else
-            GF_UPD_IO(double2);
+            GF_UPD_IO(double2, double2);
     }
 #undef GF_UPD_IO
 #undef GF_UPD
@@ -2719,11 +2764,10 @@ hipError_t launch_update_delta(const Launch &L, int link_io, int reunit)
     return hipGetLastError();
 }
 
-hipError_t launch_pack_links(const Launch &L)
+hipError_t launch_begin_call(const Launch &L, int in_caller)
 {
-    hipLaunchKernelGGL(k_begin_call, dim3((L.ncfg + 63) / 64), dim3(64), 0, L.stream, L.cfgs, L.ncfg,
-                       L.link_f32 ? 0 : 1);
-    if (L.link_f32)
+    hipLaunchKernelGGL(k_begin_call, dim3((L.ncfg + 63) / 64), dim3(64), 0, L.stream, L.cfgs, L.ncfg, in_caller);
+    if (!in_caller)
         hipLaunchKernelGGL(k_pack_links<float2>, dim3(L.total_site_blocks), dim3(kSiteBlock), 0, L.stream, L.cfgs,
                            L.batch);
     return hipGetLastError();

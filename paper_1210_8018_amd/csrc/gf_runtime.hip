@@ -620,19 +620,21 @@ void set_link_storage(gf_ctx c, int f32)
     drop_graph(c);
 }
 
-// Iterations of a call. FP64 link storage: the first update reads the
-// caller's links (no copy in), and with n_exact > 1 (gf_step: exactly that
-// many updates) the last one writes them back (no copy out); the updates in
-// between run as graph chunks. Binary32 storage copies the links into the
-// two-row buffer first. At the end, configurations whose links are in the
+// Iterations of a call. The first update reads the caller's links (no copy
+// in), and with n_exact > 1 (gf_step: exactly that many updates) the last one
+// writes them back (no copy out); the updates in between run as graph chunks.
+// A gf_fix_until call with binary32 storage copies the links into the two-row
+// buffer first. At the end, configurations whose links are in the
 // two-row buffer (the call stopped on its rule, or made one update) are
 // written back to the caller's array, third rows rebuilt.
 gf_status run_until_done(gf_ctx c, long long n_exact = 0)
 {
     gf_status st = reset_active(c);
     if (st != GF_OK) return st;
-    if (c->L.fused) HIPCHK(c, launch_pack_links(c->L));
-    const bool io = c->L.fused && !c->L.link_f32;
+    // a binary32 gf_fix_until rounds the caller's links even if no update is
+    // due, so it copies them; gf_step updates at least once
+    const bool io = c->L.fused && (!c->L.link_f32 || n_exact > 0);
+    if (c->L.fused) HIPCHK(c, launch_begin_call(c->L, io));
     // run_exact reads the control block back now and then, so the last update
     // is placed by the count at the start
     const int any_reunit = n_exact > 0 ? reunit_within(c, n_exact - 1, 1) : 0;

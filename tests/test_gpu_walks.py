@@ -32,3 +32,22 @@ def test_planned_walks_equal_single_slices(monkeypatch, dims, kw):
     assert abs(out[0][0][0] - Fr) < 1e-13 and abs(out[0][0][1] - thr) < 1e-12 * thr
     assert torch.equal(out[0][3], out[1][3])
     assert abs(out[0][1] - out[1][1]) <= 1e-15 * abs(out[1][1]) and abs(out[0][2] - out[1][2]) <= 1e-14 * out[1][2]
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 6, 4), (16, 16, 16, 32), (9, 6, 4, 27), (48, 16, 8, 8)])
+@pytest.mark.parametrize("kw", [dict(fft_prec=1), dict(), dict(fft_prec=1, reunit_every=2)])
+def test_binary32_links_in_and_out_of_a_call(dims, kw):
+    """Binary32 storage: updates that read the caller's links and write them
+    back equal those of a call that copies them in and out, bit for bit, in
+    one call and in calls of one update."""
+    U = random_links(dims, 0.3, 72)
+    U = U * np.exp(1e-3j)  # not special unitary to rounding: rows 0 and 1 alone count
+    a, b, c = (torch.from_numpy(U).to("cuda") for _ in range(3))
+    kw = dict(kw, link_prec=1, fft_schedule=3, refine_theta=1e-20)
+    fa, fb, fc = (GaugeFixer(u, **kw) for u in (a, b, c))
+    Fa = fa.step(4)
+    it, F, th = fb.fix_until(1e-20, 4, allow_maxiter=True)
+    for _ in range(4):
+        Fc = fc.step(1)
+    assert it == 4 and torch.equal(a, b) and torch.equal(a, c)
+    assert Fa == (F, th) and abs(Fa[0] - Fc[0]) < 1e-6
