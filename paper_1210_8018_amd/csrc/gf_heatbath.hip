@@ -250,36 +250,39 @@ __device__ void cm_update(M3 &u, const M3 &A, double beta, int mode, int site, i
 
 // Updates every U_MU(s) with x + y + z + t = par (mod 2); these links are
 // independent (their staples hold only other directions and other-parity
-// sites). Work-item i takes the i-th such site in lexicographic order. MODE
-// 0: heatbath, 1: overrelaxation.
+// sites). Work-items take these sites in slabs of zc xy-planes (hb_slab):
+// within a slab in lexicographic order, then the next slab. MODE 0: heatbath,
+// 1: overrelaxation.
 //
 // What bounds it: memory. A class reads every link of the other three
 // directions and half of U_MU, in two-row form 384 B per lattice site at
-// least, and writes 48; at 32^4 it moves 720 (L2 holds too few sites of a
-// t-slice to serve the second use of each link) in 118 us, 6.4 TB/s, with
-// 2900 VALU instructions per wave (40 us of issue) beside it. Reading the
-// caller's array instead (three rows, the other parity's elements between
-// this one's in every cache line) took 432 us, the parity-split copy with the
-// loads of all six staples issued first (spilled) 200 us, one staple at a
-// time (m3_fence) 124 us (three waves per SIMD), the next staple's loads in flight 117
-// us (two waves per SIMD); blocks not renumbered by XCD 132 us.
+// least, and writes 48; at 32^4 it reads 610 (L2 serves the second use of a
+// link to the sites in flight only) and takes 107 us, with 2900 VALU
+// instructions per wave (40 us of issue) beside it. In lexicographic order
+// all through it read 660 to 730 and took 114 to 118 us (hb_slab). The steps
+// to that form: reading the caller's array (three rows, the other parity's
+// elements between this one's in every cache line) 432 us; the parity-split
+// copy with the loads of all six staples issued first (spilled) 200; one
+// staple at a time (m3_fence) 124 (three waves per SIMD); the next staple's
+// loads in flight 117 (two waves per SIMD); blocks not renumbered by XCD 132.
 template <bool FULL, int MODE, int MU>
 __global__ __launch_bounds__(kSiteBlock, 2) void k_heatbath(const Cfg *__restrict__ cfgs, int par, double beta,
-                                                         uint32_t k0, uint32_t k1, long long n)
+                                                         uint32_t k0, uint32_t k1, long long n, int zc)
 {
     const Cfg &C = cfgs[0];
     const int V = C.V;
-    const int i = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (i >= V / 2) return;
+    const int w = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    if (w >= V / 2) return;
     const int L[4] = {C.dims[0], C.dims[1], C.dims[2], C.dims[3]};
     const HbGeom G = {L[0] / 2, C.V2 / 2, C.V3 / 2};
     int c[4];
-    const int row = i / G.half;
-    c[0] = i - row * G.half;
-    const int r = row / L[1];
-    c[1] = row - r * L[1];
-    c[3] = r / L[2];
-    c[2] = r - c[3] * L[2];
+    const int p = w / G.V2h, q = w - p * G.V2h;  // xy-plane of a parity, site in it
+    c[1] = q / G.half;
+    c[0] = q - c[1] * G.half;
+    const int slab = p / (zc * L[3]), z0 = slab * zc, zn = min(zc, L[2] - z0), pz = p - z0 * L[3];
+    c[3] = pz / zn;
+    c[2] = z0 + pz - c[3] * zn;
+    const int row = c[1] + L[1] * (c[2] + L[2] * c[3]), i = c[0] + G.half * row;
     const int odd = (c[1] + c[2] + c[3] + par) & 1;
     const int s = 2 * c[0] + odd + L[0] * row;
     double2 *U = hb_links(C);
@@ -471,19 +474,43 @@ __global__ __launch_bounds__(256) void k_sum_plaquette(const Cfg *__restrict__ c
     if (threadIdx.x == 0) *out = (f.hi + f.lo) / (18.0 * (double)C.V);
 }
 
+// z-planes of k_heatbath's slabs. An XCD has some 16384 sites of a class in
+// flight; numbered a t-slice after the other, where a t-slice holds that many
+// none of them finds a link that another loads as its t-neighbour. Numbered
+// slab by slab, t ahead of the slab, they are a tile of several z and several
+// t, best as long in z as in t (16384 sites of a parity / sites of an
+// xy-plane planes, its root), but not under six planes: the t beside the tile
+// are the ones loaded just before. A heatbath and four overrelaxation sweeps,
+// us, without slabs and in slabs of 3, 4, 6, 8, 16: 24^4 1937, 1838, 1834,
+// 1816, 1834, 1881; 32^4 5886, 5694, 5549, 5536, 5583, 5822; 36 x 18 x 24 x
+// 54 4679, 4522, 4440, 4454, 4469, 4525; 48^4 33967, 28592, 28603, 27403,
+// 28231, 29607; 64^3 x 16 27266, 23499, 23200, 23204, 22865, 26442; 16^2 x
+// 64^2 5704, 5789, 6322, 5713, 5474, 5456 (this one's planes are of 128
+// sites: 11). A lattice whose sites are in flight at once needs no slabs:
+// 16^3 x 32 728 without, 749 in slabs of 4.
+int hb_slab(const int *dims)
+{
+    const int V2h = dims[0] / 2 * dims[1];
+    if ((long long)V2h * dims[2] * dims[3] <= 8 * 16384) return dims[2];
+    const double nz = fmax(6.0, sqrt(16384.0 / V2h));
+    const int k = (int)(dims[2] / nz + 0.5);
+    return k <= 1 ? dims[2] : (dims[2] + k - 1) / k;
+}
+
 }  // namespace
 
-hipError_t launch_heatbath_sweep(const Launch &L, int V, int mode, int full, double beta, uint64_t seed, long long n)
+hipError_t launch_heatbath_sweep(const Launch &L, const int *dims, int mode, int full, double beta, uint64_t seed, long long n)
 {
     if (full && mode != 0) return hipErrorInvalidValue;  // a call's first sweep is a heatbath sweep
-        // single waves as work-groups where work-groups of four would not give
+    const int V = dims[0] * dims[1] * dims[2] * dims[3], zc = hb_slab(dims);
+    // single waves as work-groups where work-groups of four would not give
     // each CU one
     const int nt = V / 2 >= 256 * kSiteBlock ? kSiteBlock : 64;
     const dim3 grid((V / 2 + nt - 1) / nt), blk(nt);
     const uint32_t k0 = (uint32_t)(seed & 0xffffffffull), k1 = (uint32_t)(seed >> 32);
 #define GF_HB(FULL_, MODE_, MU_)                                                                                    \
     for (int par = 0; par < 2; ++par)                                                                               \
-        hipLaunchKernelGGL((k_heatbath<FULL_, MODE_, MU_>), grid, blk, 0, L.stream, L.cfgs, par, beta, k0, k1, n);
+        hipLaunchKernelGGL((k_heatbath<FULL_, MODE_, MU_>), grid, blk, 0, L.stream, L.cfgs, par, beta, k0, k1, n, zc);
 #define GF_HB4(FULL_, MODE_) GF_HB(FULL_, MODE_, 0) GF_HB(FULL_, MODE_, 1) GF_HB(FULL_, MODE_, 2) GF_HB(FULL_, MODE_, 3)
     if (full) {
         GF_HB4(true, 0)

@@ -244,7 +244,7 @@ hipError_t launch_momentum_table(const Launch &L);
 hipError_t launch_touch_links(const Launch &L);
 // One sweep of the generator on its copy of the links (launch_heatbath_pack
 // before the first, with `full`; launch_heatbath_unpack after the last).
-hipError_t launch_heatbath_sweep(const Launch &L, int V, int mode, int full, double beta, uint64_t seed, long long n);
+hipError_t launch_heatbath_sweep(const Launch &L, const int *dims, int mode, int full, double beta, uint64_t seed, long long n);
 hipError_t launch_heatbath_pack(const Launch &L, int nblk);
 hipError_t launch_heatbath_unpack(const Launch &L, int nblk);
 // Walks of the plaquette and of the functional: nb3 sets of kSiteBlock

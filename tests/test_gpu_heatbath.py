@@ -125,6 +125,18 @@ def test_parity_split_sweeps(dims):
     assert np.max(np.abs(Ud.cpu().numpy() - ref)) < 1e-7
 
 
+@pytest.mark.parametrize("dims", [(32, 18, 20, 24), (64, 48, 20, 6)])
+def test_slabs(dims):
+    """Lattices whose classes are taken in slabs of z-planes, with a last slab
+    that is smaller: every link is updated once, from neighbours across the
+    slabs' edges. Against the oracle; the bound is test_parity_split_sweeps'."""
+    U = hot_links(dims, 4)
+    ref = oracle.heatbath(dims, U, 5.9, 1, 0, seed=9, sweep0=0)
+    Ud = dev(U)
+    GaugeFixer(Ud).heatbath(5.9, 1, 0, seed=9)
+    assert np.max(np.abs(Ud.cpu().numpy() - ref)) < 1e-7
+
+
 @pytest.mark.parametrize("dims", [(2, 2, 2, 2), (3, 4, 6, 2), (8, 8, 4, 6), (9, 12, 4, 27), (24, 16, 12, 8)])
 def test_plaquette_walks(dims):
     """Less than a site set, ragged and whole sets, one and several slices per
