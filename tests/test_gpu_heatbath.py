@@ -125,7 +125,7 @@ def test_parity_split_sweeps(dims):
     assert np.max(np.abs(Ud.cpu().numpy() - ref)) < 1e-7
 
 
-@pytest.mark.parametrize("dims", [(32, 18, 20, 24), (64, 48, 20, 6)])
+@pytest.mark.parametrize("dims", [(32, 18, 36, 16), (64, 48, 16, 8)])
 def test_slabs(dims):
     """Lattices whose classes are taken in slabs of z-planes, with a last slab
     that is smaller: every link is updated once, from neighbours across the
