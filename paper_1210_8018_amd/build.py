@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgfix.so")
-SOURCES = ["gf_kernels.hip", "gf_fft_any.hip", "gf_functional.hip", "gf_heatbath.hip",
+SOURCES = ["gf_kernels.hip", "gf_fft_any.hip", "gf_fft_zt64.hip", "gf_functional.hip", "gf_heatbath.hip",
            "gf_runtime.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

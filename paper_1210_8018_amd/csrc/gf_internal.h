@@ -183,6 +183,7 @@ struct Launch {
     int zt_tw2, zt_tw_total;       // same for the zt pass
     int zt_reg_any;                // scaled zt pass: some configuration in k_fft_zt_reg / k_fft_zt_lines
     int xy_any, zt_any;            // some configuration has k_fft_xy_any / k_fft_zt_any passes
+    int zt64;                      // one configuration, whose 1D z and t passes of an update run as k_fft_zt64
     int xy_any_it, zt_any_it;      // ... in the iteration (not in the register passes there)
     int xy_any_elems, zt_any_elems;  // LDS elements of their tiles and twiddles
     int total_lany[2], lany_elems[2];  // work-groups per field and LDS elements of k_fft_line_any
@@ -225,6 +226,8 @@ hipError_t launch_fft_zt_any(const Launch &L, int mode, int sign, void *fields_o
 hipError_t launch_fft_line_any(const Launch &L, int axis, int mode, int sign, void *fields_override, int nfields,
                                int respect_done);
 hipError_t set_lds_limits_any();
+hipError_t launch_fft_zt64(const Launch &L, int V2, int nf, int respect_done);
+hipError_t set_lds_limits_zt64();
 // from2: from the fields k_fft_xy_any left in fields2, for its configurations
 hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override, int from2 = 0);
 hipError_t launch_update(const Launch &L, int respect_done, const double2 *g_override);

@@ -480,9 +480,13 @@ hipError_t enqueue_gauge_steps(gf_ctx c, hipStream_t s, int respect_done, double
         break;
     case kSchedXY1D:
         GF_TRY(K_FFTXY, launch_fft_xy(L, -1, nullptr, nf, rd, fold_reduce));
-        GF_TRY(K_FFT2, launch_fft_axis(L, 2, -1, 0, nullptr, nf, rd));
-        GF_TRY(K_FFT3S, launch_fft_axis(L, 3, -1, 1, nullptr, nf, rd));
-        GF_TRY(K_IFFT2, launch_fft_axis(L, 2, +1, 0, nullptr, nf, rd));
+        if (L.zt64) {
+            GF_TRY(K_FFTZT_S, launch_fft_zt64(L, c->cfg[0].V2, nf, rd));
+        } else {
+            GF_TRY(K_FFT2, launch_fft_axis(L, 2, -1, 0, nullptr, nf, rd));
+            GF_TRY(K_FFT3S, launch_fft_axis(L, 3, -1, 1, nullptr, nf, rd));
+            GF_TRY(K_IFFT2, launch_fft_axis(L, 2, +1, 0, nullptr, nf, rd));
+        }
         GF_TRY(K_IFFTXY_GAUGE, launch_fft_xy_inv_gauge(L, rd, g_override));
         break;
     default:
@@ -1046,6 +1050,13 @@ gf_status apply_schedule(gf_ctx c, int sched, const Tiles &tl)
             C.ztPad = ((r % m) + m) % m;
         }
     }
+    // 64 x 64 (z, t) planes of one FP64 lattice: one register pass for the
+    // three 1D ones, an iteration 4590 us for 5240 at 64^4, 1747 for 1967 at
+    // 48 x 32 x 64^2, 261 for 296 at 16^2 x 64^2, 107 for 117 at 8^2 x 64^2;
+    // with fewer work-groups than that (one per field and four xy-sites) the
+    // 1D passes' are shorter, 51 for 59 at 4^2 x 64^2
+    const Cfg &C0 = c->cfg[0];
+    c->L.zt64 = !c->L.fp32 && c->ncfg == 1 && tl.line_reg && C0.dims[2] == 64 && C0.dims[3] == 64 && C0.V2 >= 64;
     std::vector<int> all(c->ncfg);
     for (int k = 0; k < c->ncfg; ++k) all[k] = k;
     fill_map(c, all, c->bmap, c->L);
@@ -1545,6 +1556,7 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
                                  c->stream));
     }
     HIPCHK(c, set_lds_limits());
+    HIPCHK(c, set_lds_limits_zt64());
     HIPCHK(c, launch_arm(c->L, ncfg, 0.0, 0, 1));
     HIPCHK(c, enqueue_measure(c));
     gf_status st = read_ctrl(c);

@@ -41,3 +41,23 @@ def test_register_group_passes_match_oracle(dims, prec, sched):
         for k in range(nf):
             ref = oracle.fft4d(dims, f[k], sign)
             assert np.max(np.abs(got[k] - ref)) < tol * np.max(np.abs(ref)), (sign, k)
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 64, 64), (9, 9, 64, 64), (64, 64, 64, 64)])
+def test_planes_of_64_by_64(dims):
+    """The (z, t) pass of an FP64 update on 64 x 64 planes: whole and ragged
+    tiles of xy-sites, and planes of 64 KB, whose tiles are numbered another
+    way. g against the oracle, or where that is slow against the 1D passes of
+    another schedule (FP64 rounding, the bound of the test above)."""
+    small = int(np.prod(dims)) < 10 ** 6
+    U = random_links(dims, 0.4, 43) if small else None
+    if small:
+        Ud = torch.from_numpy(U).to("cuda")
+        ref = torch.from_numpy(oracle.gauge_from_delta(dims, oracle.delta(dims, U), ALPHA)).to("cuda")
+    else:
+        gen = torch.Generator(device="cuda").manual_seed(43)
+        T = dims[::-1]
+        Ud = torch.randn((4, 3, 3) + T, dtype=torch.complex128, device="cuda", generator=gen)
+        ref = GaugeFixer(Ud, fft_prec=0, fft_schedule=1).gauge()
+    got = GaugeFixer(Ud, fft_prec=0, fft_schedule=2).gauge()
+    assert (got - ref).abs().max().item() < 1e-13
