@@ -222,7 +222,7 @@ class GaugeFunctional(torch.autograd.Function):
         omega = omega.contiguous()
         F = gf.gf_functional_g(_functional_context(U), omega)
         ctx.save_for_backward(U, omega)
-        return torch.tensor(F, dtype=torch.float64, device=U.device)
+        return torch.full((), F, dtype=torch.float64, device=U.device)  # a fill; a copied scalar waits for the stream
 
     @staticmethod
     def backward(ctx, grad_out):
