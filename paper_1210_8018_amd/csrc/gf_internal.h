@@ -241,7 +241,7 @@ enum : int { kLinksBuffers = 0, kLinksFromCaller = 1, kLinksToCaller = 2 };
 hipError_t launch_update_delta(const Launch &L, int link_io, int reunit);
 // in_caller: the first update reads the caller's links; else they are copied
 // to binary32 two-row buffer 0
-hipError_t launch_begin_call(const Launch &L, int in_caller);
+hipError_t launch_begin_call(const Launch &L, int in_caller, double eps, long long add_iters);
 hipError_t launch_momentum_table(const Launch &L);
 // reads every configuration's two-row link buffers (cache eviction before a timed pass)
 hipError_t launch_touch_links(const Launch &L);

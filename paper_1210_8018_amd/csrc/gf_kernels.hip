@@ -17,11 +17,9 @@ namespace gfk {
 // ============================================================ control
 // Arm a fix/step call: set eps and the iteration cap, evaluate the stopping
 // rule on the latest theta. reset != 0 also clears the control block.
-__global__ void k_arm(const Cfg *__restrict__ cfgs, int ncfg, double eps, long long add_iters, int reset)
+__device__ __forceinline__ void arm(const Cfg &C, double eps, long long add_iters, int reset)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncfg) return;
-    Ctrl *ct = cfgs[c].ctrl;
+    Ctrl *ct = C.ctrl;
     if (reset) {
         ct->iter = 0;
         ct->F = 0.0;
@@ -31,7 +29,7 @@ __global__ void k_arm(const Cfg *__restrict__ cfgs, int ncfg, double eps, long l
     }
     ct->eps = eps;
     ct->max_iter = ct->iter + add_iters;
-    ct->ru_now = next_reunit(cfgs[c], ct->iter);
+    ct->ru_now = next_reunit(C, ct->iter);
     int d = kRunning;
     if (!reset) {
         if (!isfinite(ct->F) || !isfinite(ct->theta))
@@ -42,6 +40,12 @@ __global__ void k_arm(const Cfg *__restrict__ cfgs, int ncfg, double eps, long l
             d = kMaxIter;
     }
     ct->done = d;
+}
+
+__global__ void k_arm(const Cfg *__restrict__ cfgs, int ncfg, double eps, long long add_iters, int reset)
+{
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c < ncfg) arm(cfgs[c], eps, add_iters, reset);
 }
 
 // ============================================================ S1: Eq. 5 stencil + sums
@@ -2366,11 +2370,13 @@ __global__ __launch_bounds__(kSiteBlock) void k_unpack_links(const Cfg *__restri
 }
 
 // Start of an iterating call: links in buffer 0 (copied by k_pack_links) or in
-// the caller's array (read there by the first update).
-__global__ void k_begin_call(const Cfg *__restrict__ cfgs, int ncfg, int in_caller)
+// the caller's array (read there by the first update). add_iters >= 0: arms
+// the call too, which as a launch of its own cost 10 to 18 us of a call.
+__global__ void k_begin_call(const Cfg *__restrict__ cfgs, int ncfg, int in_caller, double eps, long long add_iters)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncfg) return;
+    if (add_iters >= 0) arm(cfgs[c], eps, add_iters, 0);
     Ctrl *ct = cfgs[c].ctrl;
     ct->cur = 0;
     ct->in_caller = in_caller;
@@ -2764,9 +2770,10 @@ hipError_t launch_update_delta(const Launch &L, int link_io, int reunit)
     return hipGetLastError();
 }
 
-hipError_t launch_begin_call(const Launch &L, int in_caller)
+hipError_t launch_begin_call(const Launch &L, int in_caller, double eps, long long add_iters)
 {
-    hipLaunchKernelGGL(k_begin_call, dim3((L.ncfg + 63) / 64), dim3(64), 0, L.stream, L.cfgs, L.ncfg, in_caller);
+    hipLaunchKernelGGL(k_begin_call, dim3((L.ncfg + 63) / 64), dim3(64), 0, L.stream, L.cfgs, L.ncfg, in_caller, eps,
+                       add_iters);
     if (!in_caller)
         hipLaunchKernelGGL(k_pack_links<float2>, dim3(L.total_site_blocks), dim3(kSiteBlock), 0, L.stream, L.cfgs,
                            L.batch);

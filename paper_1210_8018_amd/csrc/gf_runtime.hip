@@ -624,21 +624,25 @@ void set_link_storage(gf_ctx c, int f32)
     drop_graph(c);
 }
 
-// Iterations of a call. The first update reads the caller's links (no copy
+// Iterations of a call, armed with eps and add_iters (add_iters < 0: armed by
+// the caller). The first update reads the caller's links (no copy
 // in), and with n_exact > 1 (gf_step: exactly that many updates) the last one
 // writes them back (no copy out); the updates in between run as graph chunks.
 // A gf_fix_until call with binary32 storage copies the links into the two-row
 // buffer first. At the end, configurations whose links are in the
 // two-row buffer (the call stopped on its rule, or made one update) are
 // written back to the caller's array, third rows rebuilt.
-gf_status run_until_done(gf_ctx c, long long n_exact = 0)
+gf_status run_until_done(gf_ctx c, double eps, long long add_iters, long long n_exact = 0)
 {
     gf_status st = reset_active(c);
     if (st != GF_OK) return st;
     // a binary32 gf_fix_until rounds the caller's links even if no update is
     // due, so it copies them; gf_step updates at least once
     const bool io = c->L.fused && (!c->L.link_f32 || n_exact > 0);
-    if (c->L.fused) HIPCHK(c, launch_begin_call(c->L, io));
+    if (c->L.fused)
+        HIPCHK(c, launch_begin_call(c->L, io, eps, add_iters));
+    else if (add_iters >= 0)
+        HIPCHK(c, launch_arm(c->L, c->ncfg, eps, add_iters, 0));
     // run_exact reads the control block back now and then, so the last update
     // is placed by the count at the start
     const int any_reunit = n_exact > 0 ? reunit_within(c, n_exact - 1, 1) : 0;
@@ -683,8 +687,7 @@ gf_status fix_phases(gf_ctx c, double theta_eps, int64_t max_iter)
     for (int k = 0; k < c->ncfg; ++k) before[k] = c->h_ctrl[k].iter;
     const bool two = c->link_prec == 1 && theta_eps < c->refine_theta;
     set_link_storage(c, c->link_prec == 1 ? 1 : 0);
-    HIPCHK(c, launch_arm(c->L, c->ncfg, two ? c->refine_theta : theta_eps, max_iter, 0));
-    gf_status st = run_until_done(c);
+    gf_status st = run_until_done(c, two ? c->refine_theta : theta_eps, max_iter);
     if (st != GF_OK || !two) return st;
     std::vector<int> go(c->ncfg, 0);
     bool any = false;
@@ -706,7 +709,7 @@ gf_status fix_phases(gf_ctx c, double theta_eps, int64_t max_iter)
         if (go[k]) HIPCHK(c, launch_arm_one(c->L, k, theta_eps, max_iter - (c->h_ctrl[k].iter - before[k]), 0));
     st = read_ctrl(c);
     if (st != GF_OK) return st;
-    return run_until_done(c);
+    return run_until_done(c, theta_eps, -1);
 }
 
 // n updates after `pending` ones already launched and not yet read back:
@@ -1822,8 +1825,7 @@ gf_status gf_step(gf_ctx c, int32_t n, double *F, double *theta)
     if (c->batch) return GF_ERR_STATE;
     if (n > 0) {
         set_link_storage(c, c->link_prec == 1 ? 1 : 0);
-        HIPCHK(c, launch_arm(c->L, c->ncfg, -1.0, n, 0));
-        gf_status st = run_until_done(c, n);
+        gf_status st = run_until_done(c, -1.0, n, n);
         if (st != GF_OK) return st;
     }
     if (F) *F = c->h_ctrl[0].F;
