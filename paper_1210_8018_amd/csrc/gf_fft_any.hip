@@ -359,8 +359,8 @@ __device__ __forceinline__ int slot_index(int L, int g1, int l, int passes)
     return l;
 }
 
-// (x, y) transform of the planes of a tile of one field, from `fields` (or the
-// caller's) in place, or to fields2 (to2: the inverse pass of the iteration).
+// (x, y) transform of the planes of a tile of one field (the caller's in place;
+// the iteration's: x_pass_in, x_pass_out).
 // Tile: xyQ consecutive xy-planes (fewer in a configuration's last tile),
 // element (x, y, q) at x + Xp (y + Ly q), Xp = Lx or Lx + 1, odd: the lanes of
 // an x-line access (consecutive rows) fall on distinct LDS banks.
@@ -374,7 +374,7 @@ __device__ __forceinline__ int slot_index(int L, int g1, int l, int passes)
 // took 54 and 48 us; with the x-lines staged through LDS 71 and 55.
 template <typename T2, int SIGN>
 __global__ __launch_bounds__(kAnyThreads, 5) void k_fft_xy_any(const Cfg *__restrict__ cfgs, const Batch *__restrict__ B,
-                                                            void *fields_override, int respect_done, int nf, int to2,
+                                                            void *fields_override, int respect_done, int nf,
                                                             int take_reg, int fold)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -398,8 +398,8 @@ __global__ __launch_bounds__(kAnyThreads, 5) void k_fft_xy_any(const Cfg *__rest
     T2 *buf = (T2 *)smem;
     T2 *twx = buf + Xp * Ly * C.xyQ, *twy = twx + Lx;
     const size_t o = (size_t)f * C.V + (size_t)q0 * V2;
-    T2 *src = (T2 *)(fields_override ? fields_override : C.fields) + o;
-    T2 *dst = to2 ? (T2 *)C.fields2 + o : src;
+    const T2 *src = x_pass_in<T2>(C, fields_override, SIGN) + o;
+    T2 *dst = x_pass_out<T2>(C, fields_override, SIGN) + o;
     // x-lines of two groups come from memory into registers; whole ones
     // through LDS, where each work-item takes a line
     const int g1x = any_g1(Lx, std::is_same<T2, double2>::value);
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(kAnyThreads, 4) void k_fft_zt_any(const Cfg *__rest
     T2 *twz = buf + Tp * Lt, *twt = twz + Lz;
     fill_twiddles(twz, C, 2);
     fill_twiddles(twt, C, 3);
-    T2 *__restrict__ g = (T2 *)(fields_override ? fields_override : C.fields) + (size_t)f * C.V + i0;
+    T2 *__restrict__ g = zt_pass<T2>(C, fields_override) + (size_t)f * C.V + i0;
     __syncthreads();
     // z-lines: line (p, t); t-lines: line (p, slot of z). Lanes past a ragged
     // tile's last site read it again and store nothing.
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(kAnyThreads, 4) void k_fft_line_any(const Cfg *__re
     T2 *buf = (T2 *)smem;
     T2 *tw = buf + (any_g1(Ll, std::is_same<T2, double2>::value) == Ll ? 0 : NL * Ll);
     fill_twiddles(tw, C, axis);
-    T2 *__restrict__ g = (T2 *)(fields_override ? fields_override : C.fields) + (size_t)f * C.V;
+    T2 *__restrict__ g = zt_pass<T2>(C, fields_override) + (size_t)f * C.V;
     const T *__restrict__ Km = (const T *)C.kmom;
     __syncthreads();
     const auto start = [&](int pen) __attribute__((always_inline)) {
@@ -579,17 +579,16 @@ __global__ __launch_bounds__(kAnyThreads, 4) void k_fft_line_any(const Cfg *__re
 }
 
 template <typename T2>
-hipError_t run_xy_any(const Launch &L, int sign, void *fo, int nf, int rd, int to2, int take_reg,
-                      int fold)
+hipError_t run_xy_any(const Launch &L, int sign, void *fo, int nf, int rd, int take_reg, int fold)
 {
     const dim3 grid(L.total_xy_tiles * nf + (fold ? L.ncfg : 0));
     const size_t sh = std::max((size_t)L.xy_any_elems * sizeof(T2), (size_t)(2 * (kAnyThreads / 64) * sizeof(dd)));
     if (sign < 0)
         hipLaunchKernelGGL((k_fft_xy_any<T2, -1>), grid, dim3(kAnyThreads), sh, L.stream, L.cfgs, L.batch, fo, rd, nf,
-                           to2, take_reg, fold);
+                           take_reg, fold);
     else
         hipLaunchKernelGGL((k_fft_xy_any<T2, +1>), grid, dim3(kAnyThreads), sh, L.stream, L.cfgs, L.batch, fo, rd, nf,
-                           to2, take_reg, fold);
+                           take_reg, fold);
     return hipGetLastError();
 }
 
@@ -641,11 +640,11 @@ hipError_t set_lds_any()
 
 }  // namespace
 
-hipError_t launch_fft_xy_any(const Launch &L, int sign, void *fields_override, int nfields, int respect_done, int to2,
-                             int take_reg, int fold)
+hipError_t launch_fft_xy_any(const Launch &L, int sign, void *fields_override, int nfields, int respect_done, int take_reg,
+                             int fold)
 {
-    return L.fp32 ? run_xy_any<float2>(L, sign, fields_override, nfields, respect_done, to2, take_reg, fold)
-                  : run_xy_any<double2>(L, sign, fields_override, nfields, respect_done, to2, take_reg, fold);
+    return L.fp32 ? run_xy_any<float2>(L, sign, fields_override, nfields, respect_done, take_reg, fold)
+                  : run_xy_any<double2>(L, sign, fields_override, nfields, respect_done, take_reg, fold);
 }
 
 hipError_t launch_fft_zt_any(const Launch &L, int mode, int sign, void *fields_override, int nfields, int respect_done)

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(128 * kP, 2) void k_fft_zt64(const Cfg *__restrict_
     const double2 *__restrict__ src = (const double2 *)C.tw + C.tw_off[2];
     if (threadIdx.x < kN) tw[threadIdx.x] = src[threadIdx.x];
     const int ps = min(p, np - 1);  // a ragged tile's lanes past its last site read it again and store nothing
-    double2 *__restrict__ g = (double2 *)C.fields + (size_t)f * C.V + i0;
+    double2 *__restrict__ g = (double2 *)C.work + (size_t)f * C.V + i0;
     unsigned go = (V2 * (unsigned)(a + kN * tt) + ps) * 16u;
     double2 d[4][8];
 #pragma unroll

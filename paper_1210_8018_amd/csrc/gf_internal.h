@@ -125,7 +125,8 @@ struct Cfg {
     GF_GLOBAL double2 *U12[2];   // two-row links [4][2][3][V], two buffers (workspace)
     GF_GLOBAL float2 *U12f[2];   // the same two link buffers in single-precision storage (link_prec 1)
     GF_GLOBAL float2 *g12f;      // two-row g in single-precision storage
-    GF_GLOBAL void *fields;      // packed transform fields [4][V], double2 or float2
+    GF_GLOBAL void *fields;      // Delta of the last measurement or update, packed fields [4][V], double2 or float2
+    GF_GLOBAL void *work;        // its transform [4][V], between the passes
     GF_GLOBAL void *fields2;     // the filtered fields Delta~ [4][V] read by the fused pass
     GF_GLOBAL double2 *g;        // gauge field [3][3][V]
     GF_GLOBAL double *partials;  // [nblk_march or nblk_site][4]: (F hi, F lo, theta hi, theta lo)
@@ -218,18 +219,18 @@ hipError_t launch_fft_xy_inv_gauge(const Launch &L, int respect_done, double2 *g
 hipError_t launch_fft_zt(const Launch &L, int mode, int sign, void *fields_override, int nfields, int respect_done);
 hipError_t launch_fft_zt_scale(const Launch &L, int respect_done);
 hipError_t set_lds_limits();
-// gf_fft_any.hip. to2: results to fields2; take_reg: also configurations whose
+// gf_fft_any.hip. take_reg: also configurations whose
 // iteration runs this pass in k_fft_xy_reg / k_fft_xy_inv_reg
-hipError_t launch_fft_xy_any(const Launch &L, int sign, void *fields_override, int nfields, int respect_done, int to2,
-                             int take_reg, int fold);
+hipError_t launch_fft_xy_any(const Launch &L, int sign, void *fields_override, int nfields, int respect_done, int take_reg,
+                             int fold);
 hipError_t launch_fft_zt_any(const Launch &L, int mode, int sign, void *fields_override, int nfields, int respect_done);
 hipError_t launch_fft_line_any(const Launch &L, int axis, int mode, int sign, void *fields_override, int nfields,
                                int respect_done);
 hipError_t set_lds_limits_any();
 hipError_t launch_fft_zt64(const Launch &L, int V2, int nf, int respect_done);
 hipError_t set_lds_limits_zt64();
-// from2: from the fields k_fft_xy_any left in fields2, for its configurations
-hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override, int from2 = 0);
+// any_only: for the configurations whose inverse (x, y) pass k_fft_xy_any took
+hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override, int any_only = 0);
 hipError_t launch_update(const Launch &L, int respect_done, const double2 *g_override);
 // Where the fused pass of an update takes the old links from and puts the
 // new ones: the two-row buffers, or the caller's array

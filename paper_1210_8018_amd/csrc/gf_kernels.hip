@@ -520,17 +520,19 @@ __global__ __launch_bounds__(kFftThreads) void k_fft(const Cfg *__restrict__ cfg
     const T2 *__restrict__ gtw = (const T2 *)C.tw + C.tw_off[axis];
     for (int e = threadIdx.x; e < L; e += blockDim.x) tw[e] = gtw[e];
 
-    T2 *__restrict__ g = (T2 *)(fields_override ? fields_override : C.fields) + (size_t)field * C.V;
+    const size_t fo = (size_t)field * C.V;
+    const T2 *gi = (axis == 0 ? x_pass_in<T2>(C, fields_override, sign) : zt_pass<T2>(C, fields_override)) + fo;
+    T2 *g = (axis == 0 ? x_pass_out<T2>(C, fields_override, sign) : zt_pass<T2>(C, fields_override)) + fo;
     const bool k_fast = axis != 0;
     const int ks = k_fast ? 1 : L, ls = k_fast ? P : 1;
     size_t gbase;
     if (!k_fast) {
         gbase = (size_t)t * n;
-        tile_load_contig<T2, 1024, kFftThreads>(buf0, g + gbase, n);
+        tile_load_contig<T2, 1024, kFftThreads>(buf0, gi + gbase, n);
     } else {
         const int o = t / A.inner_chunks, ic = t % A.inner_chunks;
         gbase = (size_t)o * A.S * L + (size_t)ic * P;
-        tile_load_rows<T2, 1024, kFftThreads>(buf0, g + gbase, P, L, A.S);
+        tile_load_rows<T2, 1024, kFftThreads>(buf0, gi + gbase, P, L, A.S);
     }
     __syncthreads();
     T2 *src = buf0, *dst = buf1;
@@ -864,7 +866,8 @@ __device__ __forceinline__ bool zt_is_p2(const Cfg &C) { return is_p2(C.dims[2])
 // fold != 0: one more work-group per configuration (after the tiles) does the
 // final reduction of the previous update as k_reduce would (count, stopping
 // rule, buffer flip if fold == 2) while the tiles are transformed; the tiles
-// of a configuration that has just stopped transform once more, unused.
+// of a configuration that has just stopped transform once more, unused (to
+// `work`: its Delta stays in `fields` for the call that goes on from there).
 template <typename T2, int CAP, int TH, bool P2>
 __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(CAP / TH >= 8 ? 2 : 4))) void k_fft_xy(
     const Cfg *__restrict__ cfgs, const Batch *__restrict__ B, int sign, void *fields_override, int respect_done,
@@ -890,17 +893,19 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(CAP / TH >= 
     T2 *buf = (T2 *)smem;
     T2 *twx = buf + CAP + CAP / 8;
     T2 *twy = twx + tw2;
-    T2 *__restrict__ g = (T2 *)(fields_override ? fields_override : C.fields) + (size_t)f0 * C.V + (size_t)t * n;
+    const size_t o = (size_t)f0 * C.V + (size_t)t * n;
+    const T2 *gi = x_pass_in<T2>(C, fields_override, sign) + o;
+    T2 *g = x_pass_out<T2>(C, fields_override, sign) + o;
     constexpr int NL = tile_regs<CAP, TH>();
     T2 pre[NL], out[NL];
-    tile_fetch<T2, CAP, TH>(pre, g, n);
+    tile_fetch<T2, CAP, TH>(pre, gi, n);
     load_twiddles(twx, C, 0);
     load_twiddles(twy, C, 1);
     tile_put_padded<T2, CAP, TH>(buf, pre, n, C.dims[0], C.xyPad);
     __syncthreads();
-    for (int f = f0; f < f1; ++f, g += C.V) {
+    for (int f = f0; f < f1; ++f, gi += C.V, g += C.V) {
         const bool more = f + 1 < f1;
-        if (more) tile_fetch<T2, CAP, TH>(pre, g + C.V, n);
+        if (more) tile_fetch<T2, CAP, TH>(pre, gi + C.V, n);
         xy_transform<T2, CAP, TH, P2>(buf, twx, twy, C, C.xyQ, sign);
         // a work-item reads its own LDS slots, refills them with the next
         // field, then stores: the wait for the fetch precedes the stores
@@ -937,7 +942,7 @@ __global__ __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(CAP / TH >= 
     T2 *buf = (T2 *)smem;
     T2 *twz = buf + CAP + CAP / 8;
     T2 *twt = twz + tw2;
-    T2 *__restrict__ g = (T2 *)(fields_override ? fields_override : C.fields) + (size_t)f0 * C.V + i0;
+    T2 *__restrict__ g = zt_pass<T2>(C, fields_override) + (size_t)f0 * C.V + i0;
     // LDS layout [t][z][p] with t-planes Tp = P Lz + ztPad elements apart
     const int Tp = P * Lz + C.ztPad;
     const int rows = Lz * Lt;
@@ -1216,7 +1221,7 @@ __global__ __launch_bounds__(128 * P) __attribute__((amdgpu_waves_per_eu(P >= 4 
             for (int e = 0; e < 2; ++e) kreg[2 * k2 + e] = Km[(r + 32 * (2 * j + e + 8 * k2)) * P];
     }
     // z-pencil element n2 (z = 4 n2 + j, t = r) of field f0 in global memory
-    T2 *__restrict__ g = (T2 *)C.fields + (size_t)f0 * C.V + i0 + p + (size_t)V2 * (32 * r + j);
+    T2 *__restrict__ g = (T2 *)C.work + (size_t)f0 * C.V + i0 + p + (size_t)V2 * (32 * r + j);
     const size_t gz = (size_t)4 * V2;  // z -> z + 4
     for (int f = 0; f < nfg; ++f, g += C.V) {
         T2 R[8];
@@ -1442,7 +1447,7 @@ __global__ __launch_bounds__(256) void k_fft_line(const Cfg *__restrict__ cfgs, 
     const unsigned o = (unsigned)q;
     if (threadIdx.x < L) tw[threadIdx.x] = ((const T2 *)C.tw + C.tw_off[axis])[threadIdx.x];
     __syncthreads();
-    T2 *__restrict__ g = (T2 *)(fields_override ? fields_override : C.fields) + (size_t)field * C.V + wbase;
+    T2 *__restrict__ g = zt_pass<T2>(C, fields_override) + (size_t)field * C.V + wbase;
     T2 R[M];
     if constexpr (KIND == 1) {
 #pragma unroll
@@ -1538,7 +1543,7 @@ __global__ __launch_bounds__(P * LT * (LZ >= 32 ? 4 : 2)) void k_fft_zt_lines(co
             for (int e = 0; e < QT; ++e) kreg[QT * k2 + e] = Km[(size_t)(rt + LZ * (QT * jt + e + MT * k2)) * P];
     }
     // z-line element n2 (z = LPZ n2 + jz, t = rz) of field f0 in global memory
-    T2 *__restrict__ g = (T2 *)C.fields + (size_t)f0 * C.V + i0 + pz + (size_t)V2 * (LZ * rz + jz);
+    T2 *__restrict__ g = (T2 *)C.work + (size_t)f0 * C.V + i0 + pz + (size_t)V2 * (LZ * rz + jz);
     const size_t gz = (size_t)LPZ * V2;  // z -> z + LPZ
     for (int f = 0; f < nfg; ++f, g += C.V) {
         T2 R[MZ];
@@ -1602,10 +1607,11 @@ __host__ __device__ constexpr int xy_reg_lds_elems() { return xy_reg_planes_for(
 template <typename T2>
 __device__ __forceinline__ M3 gauge_from_fields(T2 a, T2 b, T2 d, T2 e);
 
-// Forward (x, y) transform of the four fields (kFields / ngroups of them per
-// work-group, the next one prefetched): rows x = LPL n2 + j of row y = r, then
-// columns y = LPL n2 + j of column kx = r. fold != 0: the work-groups past the
-// tiles do the final reduction of the previous update, as k_fft_xy's.
+// Forward (x, y) transform of the four fields from `fields` to `work` (kFields
+// / ngroups of them per work-group, the next one prefetched): rows x = LPL n2 +
+// j of row y = r, then columns y = LPL n2 + j of column kx = r. fold != 0: the
+// work-groups past the tiles do the final reduction of the previous update, as
+// k_fft_xy's.
 template <typename T2, int L>
 __global__ __launch_bounds__(xy_reg_threads<L>()) void k_fft_xy_reg(const Cfg *__restrict__ cfgs,
                                                                    const Batch *__restrict__ B, int respect_done,
@@ -1635,18 +1641,20 @@ __global__ __launch_bounds__(xy_reg_threads<L>()) void k_fft_xy_reg(const Cfg *_
     T2 *tw = buf + PL * L * YS;  // exp(-2 pi i e / L), the same table for x and y
     if (threadIdx.x < L) tw[threadIdx.x] = ((const T2 *)C.tw + C.tw_off[0])[threadIdx.x];
     __syncthreads();
-    T2 *__restrict__ plane = (T2 *)C.fields + (size_t)f0 * C.V + (size_t)((tile - B->off_xy[c]) * PL + pl) * (L * L);
+    const size_t po = (size_t)f0 * C.V + (size_t)((tile - B->off_xy[c]) * PL + pl) * (L * L);
+    const T2 *__restrict__ src = (const T2 *)C.fields + po;
+    T2 *__restrict__ dst = (T2 *)C.work + po;
     T2 *__restrict__ sb = buf + pl * L * YS;
     T2 Rn[M];
 #pragma unroll
-    for (int n2 = 0; n2 < M; ++n2) Rn[n2] = plane[r * L + LPL * n2 + j];
-    for (int f = 0; f < nfg; ++f, plane += C.V) {
+    for (int n2 = 0; n2 < M; ++n2) Rn[n2] = src[r * L + LPL * n2 + j];
+    for (int f = 0; f < nfg; ++f, src += C.V, dst += C.V) {
         T2 R[M];
 #pragma unroll
         for (int n2 = 0; n2 < M; ++n2) R[n2] = Rn[n2];
         if (f + 1 < nfg) {
 #pragma unroll
-            for (int n2 = 0; n2 < M; ++n2) Rn[n2] = plane[C.V + r * L + LPL * n2 + j];
+            for (int n2 = 0; n2 < M; ++n2) Rn[n2] = src[C.V + r * L + LPL * n2 + j];
         }
         line_forward<LPL, M>(R, tw, j);  // R[Q k2 + e] = (y = r, kx = Q j + e + M k2)
         if (f) __syncthreads();          // the previous field's reads of the tile are done
@@ -1661,7 +1669,7 @@ __global__ __launch_bounds__(xy_reg_threads<L>()) void k_fft_xy_reg(const Cfg *_
 #pragma unroll
         for (int k2 = 0; k2 < LPL; ++k2)
 #pragma unroll
-            for (int e = 0; e < Q; ++e) plane[(Q * j + e + M * k2) * L + r] = R[Q * k2 + e];
+            for (int e = 0; e < Q; ++e) dst[(Q * j + e + M * k2) * L + r] = R[Q * k2 + e];
     }
 }
 
@@ -1699,7 +1707,7 @@ __global__ __launch_bounds__(xy_reg_threads<L>()) void k_fft_xy_inv_reg(const Cf
     if (threadIdx.x < L) tw[threadIdx.x] = ((const T2 *)C.tw + C.tw_off[0])[threadIdx.x];
     __syncthreads();
     const size_t po = (size_t)f0 * C.V + (size_t)((tile - B->off_xy[c]) * PL + pl) * (L * L);
-    const T2 *__restrict__ src = (const T2 *)C.fields + po;
+    const T2 *__restrict__ src = (const T2 *)C.work + po;
     T2 *__restrict__ dst = (T2 *)C.fields2 + po;
     T2 *__restrict__ sb = buf + pl * L * YS;
     T2 Rn[M];
@@ -1778,7 +1786,7 @@ __device__ __forceinline__ M3 gauge_from_fields(T2 a, T2 b, T2 d, T2 e)
 
 // g goes to g_override (caller, full matrices) if given, else to the
 // workspace: two_row 2 in two-row single-precision storage (g12f), 0 full
-// (g). two_row 3: the gauge steps write the filtered fields Delta~ to fields2
+// (g). two_row 3: the gauge steps leave the filtered fields Delta~ in fields2
 // instead, and the fused pass (FP64 link storage) forms each g it needs from
 // them.
 __device__ __forceinline__ void store_gauge(const Cfg &C, double2 *g_override, int two_row, int s, const M3 &m)
@@ -1803,24 +1811,18 @@ __host__ __device__ constexpr bool reg_forms_g(const double2 *g_override, int tw
 template <typename T2>
 __global__ __launch_bounds__(kSiteBlock) void k_gauge(const Cfg *__restrict__ cfgs, const Batch *__restrict__ B,
                                                       int respect_done, double2 *__restrict__ g_override, int two_row,
-                                                      int from2)
+                                                      int any_only)
 {
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     const int c = find_cfg(B->off_site, B->n, blk);
     const Cfg &C = cfgs[B->idx[c]];
     if (respect_done && C.ctrl->done) return;
-    // from2: after k_fft_xy_any; the others' inverse pass has formed g
-    if (from2 && (!C.xy_any || (C.xy_reg && reg_forms_g<T2>(g_override, two_row)))) return;
+    // any_only: after k_fft_xy_any; the others' inverse pass has formed g
+    if (any_only && (!C.xy_any || (C.xy_reg && reg_forms_g<T2>(g_override, two_row)))) return;
     const int V = C.V;
     const int s = (blk - B->off_site[c]) * kSiteBlock + threadIdx.x;
     if (s >= V) return;
-    const T2 *__restrict__ f = (const T2 *)(from2 ? C.fields2 : C.fields);
-    if (two_row == 3 && !g_override) {  // the fused pass forms g itself
-        T2 *__restrict__ o = (T2 *)C.fields2;
-#pragma unroll
-        for (int k = 0; k < kFields; ++k) o[(size_t)k * V + s] = f[(size_t)k * V + s];
-        return;
-    }
+    const T2 *__restrict__ f = (const T2 *)C.fields2;
     const M3 m = gauge_from_fields(f[s], f[(size_t)V + s], f[(size_t)2 * V + s], f[(size_t)3 * V + s]);
     store_gauge(C, g_override, two_row, s, m);
 }
@@ -1849,7 +1851,7 @@ __global__ __launch_bounds__(TH) void k_fft_xy_inv_gauge(const Cfg *__restrict__
     T2 *buf = (T2 *)smem;
     T2 *twx = buf + CAP + CAP / 8;
     T2 *twy = twx + tw2;
-    const T2 *__restrict__ src = (const T2 *)C.fields + site0;
+    const T2 *__restrict__ src = (const T2 *)C.work + site0;
     T2 val[kFields][MS];
     T2 pre[MS];
     tile_fetch<T2, CAP, TH, MS, true>(pre, src, n);
@@ -2518,7 +2520,7 @@ static hipError_t run_xy(const Launch &L, int nf, int sign, void *fo, int rd, in
     if (fo ? L.xy_any : L.xy_any_it) {
         const int f = fold;
         fold = 0;
-        const hipError_t e = launch_fft_xy_any(L, sign, fo, nf, rd, 0, fo != nullptr, f);
+        const hipError_t e = launch_fft_xy_any(L, sign, fo, nf, rd, fo != nullptr, f);
         if (e != hipSuccess) return e;
         ++launched;
     }
@@ -2614,8 +2616,8 @@ static hipError_t run_xyg(const Launch &L, int rd, double2 *go)
     // extents up to 64: the filtered fields, and g from them unless the fused
     // pass forms it
     if (reg ? L.xy_any_it : L.xy_any) {
-        hipError_t e = launch_fft_xy_any(L, +1, nullptr, kFields, rd, 1, !reg, 0);
-        if (e == hipSuccess && (go || gm != 3)) e = launch_gauge(L, rd, go, 1);
+        hipError_t e = launch_fft_xy_any(L, +1, nullptr, kFields, rd, !reg, 0);
+        if (e == hipSuccess) e = launch_gauge(L, rd, go, 1);
         if (e != hipSuccess) return e;
         ++launched;
     }
@@ -2714,14 +2716,15 @@ hipError_t set_lds_limits()
     return e == hipSuccess ? set_lds_limits_any() : e;
 }
 
-hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override, int from2)
+hipError_t launch_gauge(const Launch &L, int respect_done, double2 *g_override, int any_only)
 {
+    if (!g_override && gauge_store_mode(L) == 3) return hipSuccess;  // the fused pass forms g
     if (L.fp32)
         hipLaunchKernelGGL(k_gauge<float2>, dim3(L.total_site_blocks), dim3(kSiteBlock), 0, L.stream, L.cfgs,
-                           L.batch, respect_done, g_override, gauge_store_mode(L), from2);
+                           L.batch, respect_done, g_override, gauge_store_mode(L), any_only);
     else
         hipLaunchKernelGGL(k_gauge<double2>, dim3(L.total_site_blocks), dim3(kSiteBlock), 0, L.stream, L.cfgs,
-                           L.batch, respect_done, g_override, gauge_store_mode(L), from2);
+                           L.batch, respect_done, g_override, gauge_store_mode(L), any_only);
     return hipGetLastError();
 }
 

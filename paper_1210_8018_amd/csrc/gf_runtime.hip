@@ -1405,8 +1405,6 @@ gf_status choose_schedule(gf_ctx c, int requested)
         }
     c->timing = timing;
     c->ev_used = 0;
-    // the fields were transformed in place: measure again so they hold Delta
-    HIPCHK(c, enqueue_measure(c));
     c->spread_groups = c->ncfg > 1;
     gf_status st = apply_schedule(c, pick.sched, pick.tiles);
     if (st != GF_OK) return st;
@@ -1474,6 +1472,8 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
     Batch &b = c->bmap;
     memset(&b, 0, sizeof(b));
     b.n = ncfg;
+    // single-precision storage exists only in the fused exchange pass
+    const bool fused = !(getenv("GF_NOFUSE") && params[0].link_prec == 0);
     int max_lds = 0;
     std::vector<std::vector<double>> sin2s(ncfg);
     std::vector<std::vector<char>> tws(ncfg);
@@ -1505,6 +1505,7 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
         C.fields = c->ws + l.fields;
         C.fields2 = c->ws + l.fields2;
         C.g = (double2 *)(c->ws + l.g);
+        C.work = fused ? (void *)C.g : (void *)C.U12[0];  // whichever the iterations do not use
         C.partials = (double *)(c->ws + l.partials);
         C.ctrl = (Ctrl *)(c->ws + ctrl_base) + k;
         C.sin2 = (const double *)(c->ws + l.sin2);
@@ -1541,8 +1542,7 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
     }
     c->L.max_lds_elems = max_lds;
     c->L.fp32 = params[0].fft_prec;
-    // single-precision storage exists only in the fused exchange pass
-    c->L.fused = (getenv("GF_NOFUSE") && params[0].link_prec == 0) ? 0 : 1;
+    c->L.fused = fused;
     c->L.link_f32 = 0;
     c->link_prec = params[0].link_prec;
     c->refine_theta = params[0].refine_theta > 0.0 ? params[0].refine_theta : 1e-10;

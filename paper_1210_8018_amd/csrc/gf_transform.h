@@ -8,9 +8,6 @@
 namespace gfk {
 
 // ============================================================ reductions + stopping rule
-// One block per configuration: sum the block partials in a fixed order,
-// F = sum/(12 V) (Eq. 1), theta = sum/(3 V) (Eq. 4); with count_iter, count
-// the update, record the history and evaluate the stopping rule theta <= eps.
 // Sum the block partials of one configuration in a fixed order (the whole
 // block takes part), F = sum/(12 V) (Eq. 1), theta = sum/(3 V) (Eq. 4); with
 // count_iter, count the update, record the history, flip the link buffer if
@@ -77,6 +74,33 @@ static __device__ __forceinline__ void finalize_config(const Cfg &C, int nparts,
             ct->done = d;
         }
     }
+}
+
+// ============================================================ the fields of a pass
+// Fields the caller gave (gf_fft) are transformed in place. In an iteration
+// the forward pass over x reads Delta from `fields` and writes to `work`, the
+// passes along y, z and t work there in place, and the backward pass over x
+// writes Delta~ to `fields2`. So Delta stays in `fields` until the next update
+// or measurement, and neither a pass launched ahead for a configuration that
+// turns out to have stopped nor a stage call (gf_gauge) between two iterating
+// calls spoils what the next update starts from. Against a transform in place
+// in `fields`, FP64: 32^4 all passes within 1 %, 16^3 x 32 the (z, t) pass 9.9
+// -> 7.6 us; with no third buffer (`work` and `fields2` the same) the backward
+// (x, y) pass of 16^3 x 32 took 8.9 us for 6.6.
+template <typename T2>
+__device__ __forceinline__ T2 *zt_pass(const Cfg &C, void *fields_override)
+{
+    return (T2 *)(fields_override ? fields_override : (void *)C.work);
+}
+template <typename T2>
+__device__ __forceinline__ const T2 *x_pass_in(const Cfg &C, void *fields_override, int sign)
+{
+    return (const T2 *)(fields_override ? fields_override : sign < 0 ? (void *)C.fields : (void *)C.work);
+}
+template <typename T2>
+__device__ __forceinline__ T2 *x_pass_out(const Cfg &C, void *fields_override, int sign)
+{
+    return (T2 *)(fields_override ? fields_override : sign < 0 ? (void *)C.work : (void *)C.fields2);
 }
 
 // ============================================================ small DFTs
