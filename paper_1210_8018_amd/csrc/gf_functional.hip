@@ -51,14 +51,26 @@ __device__ __forceinline__ Herm herm_square(const Herm &Q)
 // with p = Tr Q^2 / 2 and d = det Q reduces every power. The coefficients of
 // Q / 2^j come from the Taylor series, summed from its last term with Q
 // (s0 + s1 Q + s2 Q^2) = d s2 + (s0 + p s2) Q + s1 Q^2, and exp(2 Z) = exp(Z)^2
-// is taken j times on the coefficients, so that no matrix product is needed
-// beyond Q^2. DERIV: also the derivatives with respect to p and d.
+// is taken on the coefficients, so that no matrix product is needed beyond
+// Q^2. DERIV: also the derivatives with respect to p and d.
+//
+// At most kCoefDoublings times: where two eigenvalues of Q nearly agree, the
+// coefficients grow as 2^j and their derivatives as 8^j with the number j of
+// doublings, and cancel in what they multiply. Beyond that the matrix itself
+// is squared. Errors near lambda_8, rms, |omega| = 150 and 450: exp 3.1e-14 and
+// 7e-14 (doublings throughout 7e-13 and 8e-12, the matrix series 6e-14 and
+// 2e-13), dF/domega 5e-14 and 2e-13 (2e-12 and 2e-10; 8e-14 and 4e-13). With
+// four doublings neither is above the matrix series in any direction at any
+// size tried (|omega| 0.1 to 450), and omega of standard deviation 0.6 needs
+// no more (24^4, standard deviation 0.6 as before; 6: k_fg_backward 114 -> 125
+// us, k_expg 16 -> 20).
 struct ExpCoef {
     double2 f[3];   // of 1, Q, Q^2 of the scaled Q
     double2 fp[3];  // derivatives with respect to p ...
     double2 fd[3];  // ... and d of the scaled Q
 };
 
+constexpr int kCoefDoublings = 4;
 constexpr int kExpTerms = 16;  // |Q| <= 1/2 (scaled): the first term left out is below 1e-18
 
 __device__ __forceinline__ double2 times_i(double2 a, double s) { return make_double2(-s * a.y, s * a.x); }
@@ -131,18 +143,25 @@ struct Scaled {
     int j;
 };
 
-__device__ __forceinline__ Scaled scaled_of(const double w[8])
+// j: the smallest with |Q| <= 2^j / 2.
+__device__ __forceinline__ int doublings(const double w[8])
 {
-    Scaled s;
     double n = 0.0;
 #pragma unroll
     for (int a = 0; a < 8; ++a) n += w[a] * w[a];
     n = sqrt(2.0 * n);  // Tr Q^2 = 2 sum_a omega_a^2
-    s.j = 0;
-    while (n > 0.5 && s.j < 60) {
+    int j = 0;
+    while (n > 0.5 && j < 60) {
         n *= 0.5;
-        ++s.j;
+        ++j;
     }
+    return j;
+}
+
+__device__ __forceinline__ Scaled scaled_of(const double w[8])
+{
+    Scaled s;
+    s.j = doublings(w);
     const double sc = ldexp(1.0, -s.j);
     double v[8];
 #pragma unroll
@@ -175,6 +194,16 @@ __device__ __forceinline__ M3 exp_rows(const ExpCoef &E, const Herm &Q, const He
     return m;
 }
 
+// exp of the unscaled Q (|Q| = 2^j |scaled Q|, j > kCoefDoublings) from rows 0
+// and 1 after kCoefDoublings doublings, projected to SU(3): a squaring doubles
+// the distance from it.
+__device__ __forceinline__ void square_up(M3 &m, int j)
+{
+    m3_row2(m);
+    for (int k = kCoefDoublings; k < j; ++k) m = m3_mul(m, m);
+    m3_reunit(m);
+}
+
 __device__ __forceinline__ void load_omega(const double *__restrict__ om, int V, int s, double w[8])
 {
 #pragma unroll
@@ -193,8 +222,10 @@ __global__ __launch_bounds__(kSiteBlock) void k_expg(const Cfg *__restrict__ cfg
     load_omega(omega, C.V, s, w);
     const Scaled q = scaled_of(w);
     ExpCoef E;
-    exp_coef<false>(E, q.p, q.d, q.j);
-    m3_store12(C.g, C.V, s, exp_rows(E, q.Q, q.Q2));
+    exp_coef<false>(E, q.p, q.d, min(q.j, kCoefDoublings));
+    M3 g = exp_rows(E, q.Q, q.Q2);
+    if (q.j > kCoefDoublings) square_up(g, q.j);
+    m3_store12(C.g, C.V, s, g);
 }
 
 // Work-item of a t-walk: kSiteBlock consecutive sites of the (x, y, z) volume
@@ -220,6 +251,17 @@ __device__ __forceinline__ Walk walk_of(const Cfg &C, int blk, int nb3, int tch)
     w.b[1] = (y == 0) ? w.s3 + (Ly - 1) * Lx : w.s3 - Lx;
     w.b[2] = (z == 0) ? w.s3 + (Lz - 1) * V2 : w.s3 - V2;
     return w;
+}
+
+// a += b c
+__device__ __forceinline__ void m3_acc(M3 &a, const M3 &b, const M3 &c)
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) a.e[i * 3 + j] = cfma(b.e[i * 3 + k], c.e[k * 3 + j], a.e[i * 3 + j]);
 }
 
 // Re Tr[w gf^dag] = sum_ij Re(w_ij conj(gf_ij))
@@ -321,13 +363,34 @@ __device__ __forceinline__ M3 herm_full(const Herm &Q)
 // (dp = Tr(Q lambda_a), dd = Tr(adj(Q) lambda_a), adj(Q) = Q^2 - p, Tr lambda_a
 // = 0), so it is Re Tr(lambda_a M) with M = f1 Sigma + f2 (Sigma Q + Q Sigma)
 // + Bp Q + Bd Q^2, Bp = sum_i fp_i Tr(Q^i Sigma) and Bd alike. Everything in
-// the scaled Q, whose derivative is 2^-j lambda_a.
-__device__ __forceinline__ void omega_gradient(const double w[8], const M3 &Sig, double scale, double *__restrict__ out,
-                                               int V, int s)
+// the scaled Q, whose derivative is 2^-j lambda_a. A squaring of the matrix, g
+// = h^2, turns Re Tr[dg Sigma] into Re Tr[dh (h Sigma + Sigma h)]; the h of
+// all squarings commute, so that they can be taken from the smallest on.
+__device__ __forceinline__ void omega_gradient(double w[8], M3 &Sig, double scale, double *__restrict__ out, int V,
+                                               int s)
 {
+    if (doublings(w) > kCoefDoublings) {
+        const Scaled q = scaled_of(w);
+        ExpCoef E;
+        exp_coef<false>(E, q.p, q.d, kCoefDoublings);
+        M3 h = exp_rows(E, q.Q, q.Q2);
+        m3_reunit(h);
+        for (int k = kCoefDoublings; k < q.j; ++k) {
+            M3 a = m3_mul(h, Sig);
+            m3_fence(a);
+            m3_acc(a, Sig, h);
+            m3_fence(a);
+            Sig = a;
+            h = m3_mul(h, h);
+            m3_fence(h);
+        }
+        // Q is formed again below, not kept beside all of the above (spilled)
+#pragma unroll
+        for (int a = 0; a < 8; ++a) asm volatile("" : "+v"(w[a]));
+    }
     const Scaled q = scaled_of(w);
     ExpCoef E;
-    exp_coef<true>(E, q.p, q.d, q.j);
+    exp_coef<true>(E, q.p, q.d, min(q.j, kCoefDoublings));
     const double2 t0 = cadd(cadd(Sig.e[0], Sig.e[4]), Sig.e[8]), t1 = tr_herm(q.Q, Sig), t2 = tr_herm(q.Q2, Sig);
     const double2 Bp = cfma(E.fp[2], t2, cfma(E.fp[1], t1, cmul(E.fp[0], t0)));
     const double2 Bd = cfma(E.fd[2], t2, cfma(E.fd[1], t1, cmul(E.fd[0], t0)));
