@@ -1961,18 +1961,28 @@ gf_status gf_fft(gf_ctx c, void *d_fields, int32_t nfields, int32_t sign)
     if (c->functional_only) return GF_ERR_STATE;
     if (c->batch) return GF_ERR_STATE;
     const Launch &L = c->L;
-    switch (c->sched) {
-    case kSchedXYZT:
-        HIPCHK(c, launch_fft_xy(L, sign, d_fields, nfields, 0));
-        HIPCHK(c, launch_fft_zt(L, 0, sign, d_fields, nfields, 0));
-        break;
-    case kSchedXY1D:
-        HIPCHK(c, launch_fft_xy(L, sign, d_fields, nfields, 0));
-        HIPCHK(c, launch_fft_axis(L, 2, sign, 0, d_fields, nfields, 0));
-        HIPCHK(c, launch_fft_axis(L, 3, sign, 0, d_fields, nfields, 0));
-        break;
-    default:
-        for (int mu = 0; mu < 4; ++mu) HIPCHK(c, launch_fft_axis(L, mu, sign, 0, d_fields, nfields, 0));
+    // several passes take a tile of one field per work-group: as many fields
+    // at a time as keep a launch under 2^32 work-items
+    int tiles = std::max(L.total_xy_tiles, L.total_zt_tiles);
+    for (int a = 0; a < 2; ++a) tiles = std::max({tiles, L.total_lany[a], L.total_line[a]});
+    const int most = std::max(1, ((1 << 22) - 1) / std::max(1, tiles));  // work-groups of 1024 at most
+    const size_t field = (size_t)c->cfg[0].V * (L.fp32 ? 8 : 16);
+    for (int k = 0; k < nfields; k += most) {
+        void *f = (char *)d_fields + k * field;
+        const int n = std::min(most, nfields - k);
+        switch (c->sched) {
+        case kSchedXYZT:
+            HIPCHK(c, launch_fft_xy(L, sign, f, n, 0));
+            HIPCHK(c, launch_fft_zt(L, 0, sign, f, n, 0));
+            break;
+        case kSchedXY1D:
+            HIPCHK(c, launch_fft_xy(L, sign, f, n, 0));
+            HIPCHK(c, launch_fft_axis(L, 2, sign, 0, f, n, 0));
+            HIPCHK(c, launch_fft_axis(L, 3, sign, 0, f, n, 0));
+            break;
+        default:
+            for (int mu = 0; mu < 4; ++mu) HIPCHK(c, launch_fft_axis(L, mu, sign, 0, f, n, 0));
+        }
     }
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return GF_OK;
