@@ -1325,13 +1325,17 @@ gf_status choose_schedule(gf_ctx c, int requested)
             zs.push_back(t);
         }
     if (any_zreg)
-        for (int P : {2, 4, 8})
+        for (int P : {2, 4, 8}) {
+            bool fits = false;
+            for (const Cfg &C : c->cfg) fits = fits || zt_reg_fits(C, P);
+            if (!fits) continue;
             for (int g : {1, 2, 4}) {
                 Tiles t;
                 t.zt_reg = g;
                 t.zt_reg_p = P;
                 zs.push_back(t);
             }
+        }
     for (const Tiles &x : xs) {
         Tiles t = x;
         t.zt_reg = 0;
@@ -1348,6 +1352,7 @@ gf_status choose_schedule(gf_ctx c, int requested)
             t.zt_target = z.zt_target;
             t.zt_ept = z.zt_ept;
             t.zt_reg = z.zt_reg;
+            t.zt_reg_p = z.zt_reg_p;
             cands.push_back({kSchedXYZT, t});
         }
     }

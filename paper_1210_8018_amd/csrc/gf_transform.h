@@ -84,9 +84,11 @@ static __device__ __forceinline__ void finalize_config(const Cfg &C, int nparts,
 // or measurement, and neither a pass launched ahead for a configuration that
 // turns out to have stopped nor a stage call (gf_gauge) between two iterating
 // calls spoils what the next update starts from. Against a transform in place
-// in `fields`, FP64: 32^4 all passes within 1 %, 16^3 x 32 the (z, t) pass 9.9
-// -> 7.6 us; with no third buffer (`work` and `fields2` the same) the backward
-// (x, y) pass of 16^3 x 32 took 8.9 us for 6.6.
+// in `fields`, FP64: 32^4 all passes within 1 %; 16^3 x 32 and 24^4 the (z, t)
+// pass 9.9 -> 7.6 and 17.3 -> 16.3 us; 48^4 the forward (x, y) pass 114 -> 120.
+// With no third buffer (`work` and `fields2` the same) the backward (x, y) pass
+// of 16^3 x 32 took 8.9 us for 6.6; with non-temporal loads the forward one of
+// 24^4 17 for 13.
 template <typename T2>
 __device__ __forceinline__ T2 *zt_pass(const Cfg &C, void *fields_override)
 {

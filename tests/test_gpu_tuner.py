@@ -1,0 +1,40 @@
+"""What the transform tuner times and what a context prepares, seen from the
+kernels and runtime calls of a call."""
+from collections import Counter
+
+import pytest
+import torch
+
+from paper_1210_8018_amd.api import GaugeFixer
+from paper_1210_8018_amd.inputs import random_links
+
+pytestmark = pytest.mark.gpu
+
+
+def traced(call):
+    """Names of the kernels and runtime calls of call()."""
+    from torch.profiler import ProfilerActivity, profile
+
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+        out = call()
+        torch.cuda.synchronize()
+    names = Counter(e.name for e in p.events())
+    if not any("gfk::" in n for n in names):
+        pytest.skip("the profiler records no kernels here")
+    return out, names
+
+
+# dims no other test tunes in this process (a tuned shape is not timed again)
+@pytest.mark.parametrize("dims,widths", [((24, 3, 16, 32), (2, 4, 8)), ((12, 2, 32, 32), (2, 4, 8)),
+                                         ((18, 6, 16, 16), (2, 4)), ((6, 3, 48, 48), (2,))])
+def test_every_tile_width_of_the_register_zt_pass_is_timed(dims, widths):
+    """The widths that fit Lx Ly, and no other."""
+    U = torch.from_numpy(random_links(dims, 0.3, 3)).to("cuda")
+    fx, names = traced(lambda: GaugeFixer(U))
+    lz, lt = dims[2:]
+    for P in (2, 4, 8):
+        name = f"k_fft_zt_reg<HIP_vector_type<double, 2u>, {P}>" if lz == lt == 32 else \
+            f"k_fft_zt_lines<HIP_vector_type<double, 2u>, {lz}, {lt}, {P}>"
+        assert any(name in n for n in names) == (P in widths), (name, sorted(names))
+    fx.step(3)
