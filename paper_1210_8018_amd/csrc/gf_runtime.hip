@@ -1570,11 +1570,16 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
     gf_status st = read_ctrl(c);
     if (st != GF_OK) return st;
     if ((st = choose_schedule(c, params[0].fft_schedule)) != GF_OK) return st;
-    // the chunk graph of FP64 link storage is captured and instantiated here,
-    // not inside the first call that runs a whole chunk (about 0.3 ms, more
-    // than an iteration)
-    if (!c->noalloc && c->link_prec == 0) return build_graph(c, 0);
-    return GF_OK;
+    // the chunk graphs of FP64 link storage are captured and instantiated
+    // here, not inside a call (about 0.3 ms each, more than an iteration): the
+    // first chunk's, after the update that reads the caller's links; with one
+    // configuration, whose graphs last, also the other one if chunks with and
+    // without projections alternate
+    if (c->noalloc || c->link_prec != 0) return GF_OK;
+    const int first = reunit_within(c, fused ? 1 : 0, c->chunk);
+    if ((st = build_graph(c, first)) != GF_OK) return st;
+    const int R = params[0].reunit_every;
+    return ncfg == 1 && R > c->chunk ? build_graph(c, !first) : GF_OK;
 }
 
 // Workspace of a functional-only context: the header, g [3][3][V] and the

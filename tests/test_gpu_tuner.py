@@ -38,3 +38,17 @@ def test_every_tile_width_of_the_register_zt_pass_is_timed(dims, widths):
             f"k_fft_zt_lines<HIP_vector_type<double, 2u>, {lz}, {lt}, {P}>"
         assert any(name in n for n in names) == (P in widths), (name, sorted(names))
     fx.step(3)
+
+
+@pytest.mark.parametrize("every,built", [(0, 1), (3, 1), (8, 1), (9, 2), (20, 2)])
+def test_graphs_are_built_with_the_context(every, built):
+    """One graph per kind of chunk (of 8 updates) that the calls will run:
+    without projections, and with; none is captured inside a call."""
+    U = torch.from_numpy(random_links((8, 8, 8, 8), 0.3, 4)).to("cuda")
+    fx, names = traced(lambda: GaugeFixer(U, reunit_every=every, fft_schedule=3))
+    assert names["hipGraphInstantiate"] == built
+    for n in (60, 1, 9, 41):
+        _, names = traced(lambda: fx.step(n))
+        assert names["hipGraphInstantiate"] == 0, (n, every)
+    _, names = traced(lambda: fx.fix_until(-1.0, 50, allow_maxiter=True))
+    assert names["hipGraphInstantiate"] == 0 and names["hipGraphLaunch"] > 5
