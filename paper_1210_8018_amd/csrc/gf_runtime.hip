@@ -386,7 +386,9 @@ struct gf_ctx_s {
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> pending;
     int sched = kSched1D;
     Tiles tiles;
-    bool spread_groups = false;  // plan_groups may split tiles further than `tiles` says
+    // whether plan_groups may split tiles further than `tiles` says: never, for
+    // a list of fewer than all configurations (tuned batches), always
+    enum Spread { kSpreadNever, kSpreadReduced, kSpreadAlways } spread = kSpreadNever;
     // a context that allocates nothing (no stream, event, graph or pinned
     // host memory); iterations are launched directly on `stream`
     bool noalloc = false;
@@ -972,11 +974,11 @@ void plan_batch_walks(gf_ctx c, const std::vector<int> &list)
 }
 
 // Work-groups per tile of the register 2D passes (the four fields split among
-// them): the tuned or default number, more while the listed tiles do not give
-// every CU two. The values do not depend on it. 24^4, FP32 transform (144
-// tiles): 113 us per iteration with one (x, y) and two (z, t) work-groups per
-// tile and the reduction launched alone, 102 with four and the reduction on
-// the (x, y) pass; 16^3 x 32 59 and 49.
+// them): the tuned or default number; more, where c->spread allows it, while
+// the listed tiles do not give every CU two. The values do not depend on it.
+// 24^4, FP32 transform (144 tiles): 113 us per iteration with one (x, y) and
+// two (z, t) work-groups per tile and the reduction launched alone, 102 with
+// four and the reduction on the (x, y) pass; 16^3 x 32 59 and 49.
 void plan_groups(gf_ctx c, const std::vector<int> &list, Launch &L)
 {
     long long xy = 0, zt = 0;
@@ -984,9 +986,11 @@ void plan_groups(gf_ctx c, const std::vector<int> &list, Launch &L)
         if (c->cfg[k].xy_reg) xy += c->cfg[k].nxy;
         if (c->cfg[k].zt_reg) zt += c->cfg[k].nzt;
     }
+    const bool more = c->spread == gf_ctx_s::kSpreadAlways ||
+                      (c->spread == gf_ctx_s::kSpreadReduced && (int)list.size() < c->ncfg);
     const auto spread = [&](int g, long long tiles) {
         if (g < 1) g = 1;
-        while (c->spread_groups && tiles && g < kFields && tiles * g < 2LL * c->ncu) g *= 2;
+        while (more && tiles && g < kFields && tiles * g < 2LL * c->ncu) g *= 2;
         return g;
     };
     L.xy_reg_groups = spread(c->tiles.xy_reg, xy);
@@ -1261,14 +1265,14 @@ gf_status choose_schedule(gf_ctx c, int requested)
         requested = sched_feasible(c, kSchedXYZT) ? kSchedXYZT : sched_feasible(c, kSchedXY1D) ? kSchedXY1D : kSched1D;
     }
     if (requested != kSchedAuto) {
-        c->spread_groups = !getenv("GF_XY_REG") && !getenv("GF_ZT_REG");
+        c->spread = getenv("GF_XY_REG") || getenv("GF_ZT_REG") ? gf_ctx_s::kSpreadNever : gf_ctx_s::kSpreadAlways;
         return apply_schedule(c, requested, env_tiles());
     }
     // a tuned batch splits further once configurations have finished
     const std::string key = tune_key(c);
     for (auto &e : tune_cache())
         if (e.key == key && sched_feasible(c, e.sched) && valid_tiles(e.tiles)) {
-            c->spread_groups = c->ncfg > 1;
+            c->spread = gf_ctx_s::kSpreadReduced;
             return apply_schedule(c, e.sched, e.tiles);
         }
     struct Cand {
@@ -1410,7 +1414,7 @@ gf_status choose_schedule(gf_ctx c, int requested)
         }
     c->timing = timing;
     c->ev_used = 0;
-    c->spread_groups = c->ncfg > 1;
+    c->spread = gf_ctx_s::kSpreadReduced;
     gf_status st = apply_schedule(c, pick.sched, pick.tiles);
     if (st != GF_OK) return st;
     tune_cache().push_back({key, pick.sched, pick.tiles});

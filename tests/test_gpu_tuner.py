@@ -1,5 +1,9 @@
 """What the transform tuner times and what a context prepares, seen from the
 kernels and runtime calls of a call."""
+import json
+import os
+import subprocess
+import sys
 from collections import Counter
 
 import pytest
@@ -9,6 +13,8 @@ from paper_1210_8018_amd.api import GaugeFixer
 from paper_1210_8018_amd.inputs import random_links
 
 pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def traced(call):
@@ -52,3 +58,40 @@ def test_graphs_are_built_with_the_context(every, built):
         assert names["hipGraphInstantiate"] == 0, (n, every)
     _, names = traced(lambda: fx.fix_until(-1.0, 50, allow_maxiter=True))
     assert names["hipGraphInstantiate"] == 0 and names["hipGraphLaunch"] > 5
+
+
+BATCH = """
+import json, sys
+import torch
+from torch.profiler import ProfilerActivity, profile
+from paper_1210_8018_amd.api import BatchGaugeFixer
+from paper_1210_8018_amd.inputs import random_links
+links = [torch.from_numpy(random_links((16, 16, 16, 16), 0.3, s)).to("cuda") for s in (5, 6)]
+bx = BatchGaugeFixer(links)
+torch.cuda.synchronize()
+with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+    bx.fix_until(-1.0, 20, allow_maxiter=True)
+    torch.cuda.synchronize()
+p.export_chrome_trace(sys.argv[1])
+"""
+
+
+def test_a_tuned_batch_keeps_its_work_groups_per_tile(tmp_path):
+    """A choice read back from the tuner's file: one work-group per tile in the
+    (x, y) and (z, t) passes of 2 x 16^4, 32 and 64 tiles each, as long as both
+    configurations iterate (one more per configuration that reduces). Only the
+    launches outside graphs may carry their grid in the trace."""
+    cache, out = tmp_path / "tune", tmp_path / "trace.json"
+    cache.write_text("c64:16x16x16x16:16x16x16x16 3 1024 4 4096 8 1 4 1 1\n")
+    env = dict(os.environ, GF_AUTOTUNE_CACHE=str(cache), PYTHONPATH=ROOT)
+    r = subprocess.run([sys.executable, "-c", BATCH, str(out)], env=env, cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr
+    grids = {"k_fft_xy_reg": set(), "k_fft_xy_inv_reg": set(), "k_fft_zt_lines": set()}
+    for e in json.loads(out.read_text())["traceEvents"]:
+        for k in grids:
+            if k + "<" in e.get("name", "") and "grid" in e.get("args", {}):
+                grids[k].add(e["args"]["grid"][0])
+    if not any(grids.values()):
+        pytest.skip("the profiler records no kernels here")
+    assert grids["k_fft_xy_inv_reg"] == {64} and grids["k_fft_zt_lines"] == {128}
+    assert grids["k_fft_xy_reg"] in ({64}, {64, 66})
