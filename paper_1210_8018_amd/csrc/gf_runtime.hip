@@ -141,6 +141,8 @@ int plan_walks(const int dims[4], int nb3, bool f64_links, int resident)
 // kSiteBlock consecutive sites is fewer than 8 whole x-rows, or not whole ones
 // (see fill_map).
 bool wants_pair(const int dims[4]) { return kSiteBlock % dims[0] != 0 || kSiteBlock / dims[0] < 8; }
+// and has blocks for most CUs in pairs (18^4 in 184 blocks: 43 us, in pairs 54)
+bool enough_for_pairs(long long blocks, int ncu) { return 2 * blocks >= 3LL * ncu; }
 
 // Walks of the plaquette and the functional: as above, and long enough that
 // the blocks' sums (two doubles each) fit the 4 nblk_site doubles of partials
@@ -885,8 +887,7 @@ void fill_map(gf_ctx c, const std::vector<int> &list, Batch &b, Launch &L)
             can = C.tile[0] == 0 && C.nb3 % 2 == 0;
             want = want && wants_pair(C.dims);
         }
-        // pairs need blocks for most CUs (18^4 in 184 blocks: 43 us, in pairs 54)
-        const bool enough = 2LL * b.off_march[b.n] >= 3LL * c->ncu;
+        const bool enough = enough_for_pairs(b.off_march[b.n], c->ncu);
         L.march_pair = !can ? 0 : force == 1 ? 1 : !enough ? 0 : want ? 1 : 2;
     }
     for (int mu = 0; mu < 4; ++mu) L.total_fft_tiles[mu] = b.off_fft[mu][b.n];
@@ -1498,11 +1499,15 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
         C.nb3 = plan_tile(p.dims, C.tile, C.ntile);
         C.nch = plan_walks(p.dims, C.nb3, p.link_prec == 0, kMarchResidentPerCU * c->ncu);
         // an empty site set where an odd number would keep the fused pass
-        // from pairing them, where the blocks run in one round (36 x 18 x 24 x
-        // 54, 61 sets: 161 -> 157 us; 36^4, 183 sets in 7 rounds, would go from
-        // 327 to 332) and the partial sums hold them
-        if (ncfg == 1 && C.tile[0] == 0 && C.nb3 % 2 && C.nb3 >= 32 && wants_pair(p.dims) &&
-            (C.nb3 + 1) * C.nch <= kMarchResidentPerCU * c->ncu && (C.nb3 + 1) * C.nch <= C.nb3 * p.dims[3])
+        // from pairing them, where the blocks are enough for pairs and run in
+        // one round (an iteration, us: 61 sets, 36 x 18 x 24 x 54, 264 -> 258;
+        // 27 sets, 48 x 12^2 x 64, 158 -> 155; 11 sets, 12^2 x 18 x 64, 85.6 ->
+        // 82.7; 23 to 35 sets of seven other lattices 0 to 2 % shorter, none
+        // longer; 36^4, 183 sets in 7 rounds, its fused pass 327 -> 332) and the
+        // partial sums hold them
+        const int padded = (C.nb3 + 1) * C.nch;
+        if (ncfg == 1 && C.tile[0] == 0 && C.nb3 % 2 && wants_pair(p.dims) && enough_for_pairs(padded, c->ncu) &&
+            padded <= kMarchResidentPerCU * c->ncu && padded <= C.nb3 * p.dims[3])
             C.nb3 += 1;
         C.nblk_march = C.nb3 * C.nch;
         C.U = (double2 *)links[k];

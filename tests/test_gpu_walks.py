@@ -51,3 +51,10 @@ def test_binary32_links_in_and_out_of_a_call(dims, kw):
         Fc = fc.step(1)
     assert it == 4 and torch.equal(a, b) and torch.equal(a, c)
     assert Fa == (F, th) and abs(Fa[0] - Fc[0]) < 1e-6
+
+
+@pytest.mark.parametrize("dims", [(12, 12, 18, 64), (12, 9, 6, 256), (18, 18, 18, 48)])
+@pytest.mark.parametrize("kw", [dict(), dict(fft_prec=1, link_prec=1), dict(reunit_every=2)])
+def test_few_site_sets_with_an_empty_one(monkeypatch, dims, kw):
+    """11, 3 and 23 site sets, padded to pairs."""
+    test_planned_walks_equal_single_slices(monkeypatch, dims, kw)
