@@ -97,6 +97,11 @@ __device__ bool kp_draw(double a, int site, int mu, int k, long long n, uint32_t
 // (768 bytes per site for 576 needed), which hold nothing between calls.
 __device__ __forceinline__ double2 *hb_links(const Cfg &C) { return C.U12[0]; }
 
+// What a class reads and writes: the caller's array (a call of one sweep of a
+// small lattice), the copy as the caller's full matrices (the first of several
+// sweeps), the copy in two-row form.
+enum HbForm : int { kHbCaller, kHbFull, kHbTwoRow };
+
 // Element s of the copy: site of parity par, (xh, row) = (x / 2, y + Ly (z + Lz t)).
 struct HbGeom {
     int half, V2h, V3h;  // Lx / 2 sites of a parity per row; per xy-plane; per (x, y, z) volume
@@ -145,6 +150,19 @@ __device__ __forceinline__ int hb_hop(const HbGeom &G, const int *L, const int (
     }
 }
 
+// Where the half of a parity begins, and the element of index i there whose x
+// is 2 xh + odd (the caller's array is not split: 2 i + odd).
+template <HbForm F>
+__device__ __forceinline__ int hb_half(int V, int par)
+{
+    return F == kHbCaller || !par ? 0 : V / 2;
+}
+template <HbForm F>
+__device__ __forceinline__ int hb_element(int i, int odd)
+{
+    return F == kHbCaller ? 2 * i + odd : i;
+}
+
 // The three links of one staple of direction NU of U_MU(s): the upper one
 // U_nu(s+mu) U_mu^dag(s+nu) U_nu^dag(s), or (LOWER) U_nu^dag(s+mu-nu)
 // U_mu^dag(s-nu) U_nu(s-nu). i: index of s in the half `par`; ip: of s + mu
@@ -154,18 +172,19 @@ struct Staple {
     M3 a, b, c;
 };
 
-template <bool FULL, int MU, int NU, bool LOWER>
+template <HbForm F, int MU, int NU, bool LOWER>
 __device__ __forceinline__ Staple load_staple(const double2 *U, const HbGeom &G, const int *L, int V, int par,
                                               const int (&c)[4], int odd, int i, int ip)
 {
-    const double2 *own = U + (par ? V / 2 : 0);
-    const double2 *oth = U + (par ? 0 : V / 2);
+    constexpr bool FULL = F != kHbTwoRow;
+    const double2 *own = U + hb_half<F>(V, par);
+    const double2 *oth = U + hb_half<F>(V, 1 - par);
     const double2 *ownn = own + (size_t)NU * 9 * V, *othn = oth + (size_t)NU * 9 * V, *othm = oth + (size_t)MU * 9 * V;
     Staple S;
     if constexpr (!LOWER) {
-        S.a = hb_load<FULL>(othn, V, ip);
-        S.b = hb_load<FULL>(othm, V, hb_hop<NU, +1>(G, L, c, odd, i));
-        S.c = hb_load<FULL>(ownn, V, i);
+        S.a = hb_load<FULL>(othn, V, hb_element<F>(ip, MU == 0 ? 1 - odd : odd));
+        S.b = hb_load<FULL>(othm, V, hb_element<F>(hb_hop<NU, +1>(G, L, c, odd, i), NU == 0 ? 1 - odd : odd));
+        S.c = hb_load<FULL>(ownn, V, hb_element<F>(i, odd));
     } else {
         const int im = hb_hop<NU, -1>(G, L, c, odd, i);
         // s + mu: x is odd there where it is not at s (mu = x), else as at s
@@ -177,9 +196,10 @@ __device__ __forceinline__ Staple load_staple(const double2 *U, const HbGeom &G,
         } else {
             cp[MU] = (c[MU] + 1 == L[MU]) ? 0 : c[MU] + 1;
         }
-        S.a = hb_load<FULL>(ownn, V, hb_hop<NU, -1>(G, L, cp, oddp, ip));
-        S.b = hb_load<FULL>(othm, V, im);
-        S.c = hb_load<FULL>(othn, V, im);
+        const int em = hb_element<F>(im, NU == 0 ? 1 - odd : odd);
+        S.a = hb_load<FULL>(ownn, V, hb_element<F>(hb_hop<NU, -1>(G, L, cp, oddp, ip), NU == 0 ? 1 - oddp : oddp));
+        S.b = hb_load<FULL>(othm, V, em);
+        S.c = hb_load<FULL>(othn, V, em);
     }
     return S;
 }
@@ -265,10 +285,11 @@ __device__ void cm_update(M3 &u, const M3 &A, double beta, int mode, int site, i
 // copy with the loads of all six staples issued first (spilled) 200; one
 // staple at a time (m3_fence) 124 (three waves per SIMD); the next staple's
 // loads in flight 117 (two waves per SIMD); blocks not renumbered by XCD 132.
-template <bool FULL, int MODE, int MU>
+template <HbForm F, int MODE, int MU>
 __global__ __launch_bounds__(kSiteBlock, 2) void k_heatbath(const Cfg *__restrict__ cfgs, int par, double beta,
                                                          uint32_t k0, uint32_t k1, long long n, int zc)
 {
+    constexpr bool FULL = F != kHbTwoRow;
     const Cfg &C = cfgs[0];
     const int V = C.V;
     const int w = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
@@ -285,11 +306,11 @@ __global__ __launch_bounds__(kSiteBlock, 2) void k_heatbath(const Cfg *__restric
     const int row = c[1] + L[1] * (c[2] + L[2] * c[3]), i = c[0] + G.half * row;
     const int odd = (c[1] + c[2] + c[3] + par) & 1;
     const int s = 2 * c[0] + odd + L[0] * row;
-    double2 *U = hb_links(C);
+    double2 *U = F == kHbCaller ? C.U : hb_links(C);
     const int ip = hb_hop<MU, +1>(G, L, c, odd, i);
     M3 A = m3_zero();
     constexpr int N0 = MU == 0 ? 1 : 0, N1 = MU <= 1 ? 2 : 1, N2 = MU <= 2 ? 3 : 2;
-#define GF_LOAD(NU_, LO_) load_staple<FULL, MU, NU_, LO_>(U, G, L, V, par, c, odd, i, ip)
+#define GF_LOAD(NU_, LO_) load_staple<F, MU, NU_, LO_>(U, G, L, V, par, c, odd, i, ip)
     if constexpr (FULL) {
         Staple S = GF_LOAD(N0, false);
         add_staple<FULL, false>(A, S);
@@ -318,14 +339,15 @@ __global__ __launch_bounds__(kSiteBlock, 2) void k_heatbath(const Cfg *__restric
         add_staple<FULL, true>(A, S1);
     }
 #undef GF_LOAD
-    double2 *Um = U + (size_t)MU * 9 * V + (par ? V / 2 : 0);
-    M3 u = hb_load<FULL>(Um, V, i);
+    double2 *Um = U + (size_t)MU * 9 * V + hb_half<F>(V, par);
+    const int e = hb_element<F>(i, odd);
+    M3 u = hb_load<FULL>(Um, V, e);
     if constexpr (!FULL) m3_row2(u);
     cm_update(u, A, beta, MODE, s, MU, n, k0, k1);
     if constexpr (FULL)
-        m3_store(Um, V, i, u);
+        m3_store(Um, V, e, u);
     else
-        m3_store12(Um, V, i, u);
+        m3_store12(Um, V, e, u);
 }
 
 // Index in the generator's copy of the caller's site s.
@@ -497,41 +519,54 @@ int hb_slab(const int *dims)
     return k <= 1 ? dims[2] : (dims[2] + k - 1) / k;
 }
 
-}  // namespace
-
-hipError_t launch_heatbath_sweep(const Launch &L, const int *dims, int mode, int full, double beta, uint64_t seed, long long n)
+// One sweep, in place in the caller's array (form kHbCaller) or in the copy.
+hipError_t heatbath_sweep(const Launch &L, const int *dims, int mode, HbForm form, double beta, uint64_t seed, long long n)
 {
-    if (full && mode != 0) return hipErrorInvalidValue;  // a call's first sweep is a heatbath sweep
     const int V = dims[0] * dims[1] * dims[2] * dims[3], zc = hb_slab(dims);
     // single waves as work-groups where work-groups of four would not give
     // each CU one
     const int nt = V / 2 >= 256 * kSiteBlock ? kSiteBlock : 64;
     const dim3 grid((V / 2 + nt - 1) / nt), blk(nt);
     const uint32_t k0 = (uint32_t)(seed & 0xffffffffull), k1 = (uint32_t)(seed >> 32);
-#define GF_HB(FULL_, MODE_, MU_)                                                                                    \
+#define GF_HB(F_, MODE_, MU_)                                                                                    \
     for (int par = 0; par < 2; ++par)                                                                               \
-        hipLaunchKernelGGL((k_heatbath<FULL_, MODE_, MU_>), grid, blk, 0, L.stream, L.cfgs, par, beta, k0, k1, n, zc);
-#define GF_HB4(FULL_, MODE_) GF_HB(FULL_, MODE_, 0) GF_HB(FULL_, MODE_, 1) GF_HB(FULL_, MODE_, 2) GF_HB(FULL_, MODE_, 3)
-    if (full) {
-        GF_HB4(true, 0)
+        hipLaunchKernelGGL((k_heatbath<F_, MODE_, MU_>), grid, blk, 0, L.stream, L.cfgs, par, beta, k0, k1, n, zc);
+#define GF_HB4(F_, MODE_) GF_HB(F_, MODE_, 0) GF_HB(F_, MODE_, 1) GF_HB(F_, MODE_, 2) GF_HB(F_, MODE_, 3)
+    if (form == kHbCaller) {
+        GF_HB4(kHbCaller, 0)
+    } else if (form == kHbFull) {
+        GF_HB4(kHbFull, 0)
     } else if (mode == 0) {
-        GF_HB4(false, 0)
+        GF_HB4(kHbTwoRow, 0)
     } else {
-        GF_HB4(false, 1)
+        GF_HB4(kHbTwoRow, 1)
     }
 #undef GF_HB4
 #undef GF_HB
     return hipGetLastError();
 }
 
-hipError_t launch_heatbath_pack(const Launch &L, int nblk)
-{
-    hipLaunchKernelGGL(k_hb_pack, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs);
-    return hipGetLastError();
-}
+// A call of one heatbath sweep works in place up to this many sites: the two
+// launches of the copy cost more than the sweep gains (us of such a call, in
+// place and with the copy: 4^4 148 and 162, 8^4 152 and 175, 12^4 162 and 182,
+// 16^4 215 and 219; 16^3 x 32 356 and 299, 24^4 944 and 745).
+constexpr int kHbInPlace = 65536;
 
-hipError_t launch_heatbath_unpack(const Launch &L, int nblk)
+}  // namespace
+
+hipError_t launch_heatbath(const Launch &L, const int *dims, int nblk, double beta, int n_sweeps, int n_or, uint64_t seed,
+                           long long sweep0)
 {
+    if (n_sweeps <= 0) return hipSuccess;
+    const int V = dims[0] * dims[1] * dims[2] * dims[3];
+    if (n_sweeps == 1 && n_or == 0 && V <= kHbInPlace) return heatbath_sweep(L, dims, 0, kHbCaller, beta, seed, sweep0);
+    hipLaunchKernelGGL(k_hb_pack, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs);
+    hipError_t e = hipGetLastError();
+    for (int i = 0; i < n_sweeps && e == hipSuccess; ++i) {
+        e = heatbath_sweep(L, dims, 0, i == 0 ? kHbFull : kHbTwoRow, beta, seed, sweep0 + i);
+        for (int r = 0; r < n_or && e == hipSuccess; ++r) e = heatbath_sweep(L, dims, 1, kHbTwoRow, beta, seed, 0);
+    }
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_hb_unpack, dim3(nblk), dim3(kSiteBlock), 0, L.stream, L.cfgs);
     return hipGetLastError();
 }

@@ -246,11 +246,10 @@ hipError_t launch_begin_call(const Launch &L, int in_caller, double eps, long lo
 hipError_t launch_momentum_table(const Launch &L);
 // reads every configuration's two-row link buffers (cache eviction before a timed pass)
 hipError_t launch_touch_links(const Launch &L);
-// One sweep of the generator on its copy of the links (launch_heatbath_pack
-// before the first, with `full`; launch_heatbath_unpack after the last).
-hipError_t launch_heatbath_sweep(const Launch &L, const int *dims, int mode, int full, double beta, uint64_t seed, long long n);
-hipError_t launch_heatbath_pack(const Launch &L, int nblk);
-hipError_t launch_heatbath_unpack(const Launch &L, int nblk);
+// n_sweeps times a heatbath sweep (numbers from sweep0) and n_or
+// overrelaxation sweeps of the caller's links
+hipError_t launch_heatbath(const Launch &L, const int *dims, int nblk, double beta, int n_sweeps, int n_or, uint64_t seed,
+                           long long sweep0);
 // Walks of the plaquette and of the functional: nb3 sets of kSiteBlock
 // consecutive sites of the (x, y, z) volume, tch t-slices (a divisor of Lt)
 // per block.

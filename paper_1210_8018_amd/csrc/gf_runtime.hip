@@ -1950,12 +1950,7 @@ gf_status gf_heatbath(gf_ctx c, double beta, int32_t n_sweeps, int32_t n_or, uin
     const Cfg &C = c->cfg[0];
     for (int mu = 0; mu < 4; ++mu)
         if (C.dims[mu] % 2) return GF_ERR_SHAPE;
-    if (n_sweeps > 0) HIPCHK(c, launch_heatbath_pack(c->L, C.nblk_site));
-    for (int i = 0; i < n_sweeps; ++i) {
-        HIPCHK(c, launch_heatbath_sweep(c->L, C.dims, 0, i == 0, beta, seed, (long long)(sweep0 + i)));
-        for (int r = 0; r < n_or; ++r) HIPCHK(c, launch_heatbath_sweep(c->L, C.dims, 1, 0, beta, seed, 0));
-    }
-    if (n_sweeps > 0) HIPCHK(c, launch_heatbath_unpack(c->L, C.nblk_site));
+    HIPCHK(c, launch_heatbath(c->L, C.dims, C.nblk_site, beta, n_sweeps, n_or, seed, sweep0));
     // the links changed: measure them again, as after any other change
     HIPCHK(c, enqueue_measure(c));
     return read_ctrl(c);

@@ -154,3 +154,17 @@ def test_plaquette_walks(dims):
     ctx = gf.gf_init_functional(p, Ud, ws)
     assert abs(gf.gf_plaquette(ctx) - ref) < 1e-13
     gf.gf_destroy(ctx)
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 8, 2), (8, 8, 8, 8), (16, 16, 16, 16), (16, 16, 16, 18)])
+def test_one_sweep_calls_equal_one_call(dims):
+    """A call of one sweep works in place on small lattices, on a copy of the
+    links otherwise; the same links bit for bit as two sweeps in one call (on the
+    copy)."""
+    U = hot_links(dims, 95)
+    a, b = dev(U), dev(U)
+    fa, fb = GaugeFixer(a, fft_schedule=1), GaugeFixer(b, fft_schedule=1)
+    fa.heatbath(6.0, 2, 0, seed=11, sweep0=3)
+    fb.heatbath(6.0, 1, 0, seed=11, sweep0=3)
+    fb.heatbath(6.0, 1, 0, seed=11, sweep0=4)
+    assert torch.equal(a, b) and fa.functional() == fb.functional()
