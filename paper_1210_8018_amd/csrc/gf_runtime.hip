@@ -1449,7 +1449,9 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
     c->stream = (hipStream_t)stream;
     c->ws = (char *)d_ws;
     c->ws_bytes = ws_bytes;
-    c->chunk = params[0].chunk > 0 ? params[0].chunk : kDefaultChunk;
+    // a call's first and last updates are launched besides its chunks, before
+    // the history ring is read
+    c->chunk = std::min(params[0].chunk > 0 ? params[0].chunk : kDefaultChunk, kHist - 2);
     if (c->noalloc) {
         c->h_ctrl = new Ctrl[ncfg];
     } else {

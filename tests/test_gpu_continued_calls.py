@@ -94,3 +94,17 @@ def test_batch_goes_on(prec, sched):
         assert torch.equal(bl[k], sl[k])
         (Fb, Tb), (Fs, Ts) = bx.history(k), f.history()
         assert np.max(np.abs(np.subtract(Fb, Fs))) <= 1e-15 and np.max(np.abs(np.divide(Tb, Ts) - 1)) <= 1e-12
+
+
+@pytest.mark.parametrize("chunk", [1, 254, 255, 256])
+def test_history_of_any_chunk_length(chunk):
+    """As many (F, theta) as updates, the same for every chunk length that is
+    taken (256: the length of the device's history ring)."""
+    U = random_links((4, 4, 4, 4), 0.3, 521)
+    out = []
+    for n in (8, chunk):
+        fx = GaugeFixer(dev(U), chunk=n, fft_schedule=3)
+        fx.fix_until(-1.0, 600, allow_maxiter=True)
+        fx.step(514)
+        out.append(fx.history())
+    assert len(out[0][0]) == 1 + 600 + 514 and out[0] == out[1]
