@@ -79,10 +79,16 @@ typedef struct {
                              (x,y) 2D pass of schedules 2 and 3 also forms g
                              (in the iteration with FP64 link storage it
                              writes the filtered fields, from which the link
-                             update forms g). Lines of 16, 24, 32, 48 and 64
-                             points, and (z,t) planes of 16x16, 24x24, 32x32,
-                             16x32 and 48x48, run with their radix stages in
-                             registers.
+                             update forms g). Lines up to 64 points run with
+                             their radix stages in registers: spread over the
+                             lanes of a wave in (x,y) planes with Lx = Ly of
+                             16, 24, 32, 48 or 64, in (z,t) planes of 16x16,
+                             24x24, 32x32, 16x32 and (0 only) 48x48, and in z
+                             and t lines of those lengths; else as groups of a
+                             work-item's registers. The FP64 z and t passes of
+                             schedules 0 and 2 on 64x64 (z,t) planes of one
+                             lattice are a single pass. Longer lines are
+                             staged through LDS.
                              Schedules 2 and 3 need Lx*Ly <= 4096 (and
                              Lz*Lt <= 4096 for 3); GF_ERR_SHAPE otherwise.   */
     int32_t link_prec;    /* 0: links and g stored in FP64. 1: stored in

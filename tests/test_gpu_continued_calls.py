@@ -57,6 +57,14 @@ def test_fix_until_goes_on_after_any_stop(dims, kw, sched):
 
 
 @pytest.mark.parametrize("sched", [1, 2, 3])
+@pytest.mark.parametrize("dims", [(8, 8, 8, 8), (24, 24, 4, 6), (72, 4, 4, 6)])
+def test_separate_update_and_divergence_go_on(monkeypatch, dims, sched):
+    monkeypatch.setenv("GF_NOFUSE", "1")
+    for kw in (dict(), dict(fft_prec=1)):
+        test_fix_until_goes_on_after_any_stop(dims, kw, sched)
+
+
+@pytest.mark.parametrize("sched", [1, 2, 3])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_stage_calls_leave_the_next_update_as_it_was(prec, sched):
     """gauge() measures Delta as functional() does; an update after either is the same."""
