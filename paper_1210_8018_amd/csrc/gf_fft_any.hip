@@ -368,8 +368,8 @@ __device__ __forceinline__ int slot_index(int L, int g1, int l, int passes)
 // registers throughout (k_fft_xy_reg). fold: as in k_fft_xy.
 //
 // What bounds it: latency of memory with five waves per SIMD (its waves wait
-// for it 70 % of their lives; no LDS bank conflicts). 36^4 FP64 52 us forward
-// and 44 back (4.1 and 4.9 TB/s; LDS-staged 92 and 105), 12^4 10 and 8 us
+// for it 70 % of their lives; no LDS bank conflicts). 36^4 FP64 56 us forward
+// and 43 back (3.8 and 5.0 TB/s; LDS-staged 92 and 105), 12^4 10 and 8 us
 // (19 and 21: 21 work-groups of four fields each). At four waves per SIMD 36^4
 // took 54 and 48 us; with the x-lines staged through LDS 71 and 55.
 template <typename T2, int SIGN>

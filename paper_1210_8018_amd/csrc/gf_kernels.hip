@@ -1707,14 +1707,14 @@ __global__ __launch_bounds__(xy_reg_threads<L>()) void k_fft_xy_inv_reg(const Cf
     if (threadIdx.x < L) tw[threadIdx.x] = ((const T2 *)C.tw + C.tw_off[0])[threadIdx.x];
     __syncthreads();
     const size_t po = (size_t)f0 * C.V + (size_t)((tile - B->off_xy[c]) * PL + pl) * (L * L);
-    const T2 *__restrict__ src = (const T2 *)C.work + po;
-    T2 *__restrict__ dst = (T2 *)C.fields2 + po;
+    const T2 *src = (const T2 *)C.work + po;  // may be dst: a field's stores follow the barrier after its loads
+    T2 *dst = (T2 *)C.fields2 + po;
     T2 *__restrict__ sb = buf + pl * L * YS;
     T2 Rn[M];
 #pragma unroll
     for (int k2 = 0; k2 < LPL; ++k2)
 #pragma unroll
-        for (int e = 0; e < Q; ++e) Rn[Q * k2 + e] = ld_stream(src + (Q * j + e + M * k2) * L + r);
+        for (int e = 0; e < Q; ++e) Rn[Q * k2 + e] = src[(Q * j + e + M * k2) * L + r];
     // field f: the prefetched columns in, the next field's prefetched, the
     // rows of this work-item out in R (y = r, x = LPL n2 + j)
     auto field = [&](int f, int nf, T2 (&R)[M]) {
@@ -1725,7 +1725,7 @@ __global__ __launch_bounds__(xy_reg_threads<L>()) void k_fft_xy_inv_reg(const Cf
             for (int k2 = 0; k2 < LPL; ++k2)
 #pragma unroll
                 for (int e = 0; e < Q; ++e)
-                    Rn[Q * k2 + e] = ld_stream(src + (size_t)(f + 1) * C.V + (Q * j + e + M * k2) * L + r);
+                    Rn[Q * k2 + e] = src[(size_t)(f + 1) * C.V + (Q * j + e + M * k2) * L + r];
         }
         line_backward<LPL, M>(R, tw, j);  // R[n2] = (y = LPL n2 + j, kx = r)
         if (f) __syncthreads();
@@ -1851,7 +1851,7 @@ __global__ __launch_bounds__(TH) void k_fft_xy_inv_gauge(const Cfg *__restrict__
     T2 *buf = (T2 *)smem;
     T2 *twx = buf + CAP + CAP / 8;
     T2 *twy = twx + tw2;
-    const T2 *__restrict__ src = (const T2 *)C.work + site0;
+    const T2 *src = (const T2 *)C.work + site0;
     T2 val[kFields][MS];
     T2 pre[MS];
     tile_fetch<T2, CAP, TH, MS, true>(pre, src, n);
@@ -1871,7 +1871,7 @@ __global__ __launch_bounds__(TH) void k_fft_xy_inv_gauge(const Cfg *__restrict__
         }
     }
     if (two_row == 3 && !g_override) {
-        T2 *__restrict__ dst = (T2 *)C.fields2 + site0;
+        T2 *dst = (T2 *)C.fields2 + site0;
 #pragma unroll
         for (int f = 0; f < kFields; ++f) tile_store_regs<T2, CAP, TH>(dst + (size_t)f * C.V, val[f], n);
         return;

@@ -1441,6 +1441,16 @@ gf_status read_ncu(gf_ctx c)
     return GF_OK;
 }
 
+// Lattices whose transform has a buffer of its own between `fields` and
+// `fields2`, three sets of fields up to this size; a larger one is transformed
+// in fields2, as three sets pass the 256 MB infinity cache where two fit. An
+// iteration with the third buffer and without, us, FP64: 16^3 x 32 52.8 and
+// 56.4, 24^3 x 16 85.0 and 89.8, 24^4 113.3 and 115.3, 24^2 x 32^2 (113 MB)
+// 174.2 and 174.5; 32^3 x 24 (151 MB) 218.0 and 217.6, 32^4 (201 MB) 257.6 and
+// 254.8, 48^2 x 32^2 (453 MB) 668 and 639; FP32 transform: 32^3 x 16 125.8 and
+// 129.3, 32^4 (101 MB) 220.3 and 220.1, 36^4 (161 MB) 429 and 426.
+constexpr double kThirdFieldsBytes = 128.0 * (1 << 20);
+
 gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links, void *d_ws, size_t ws_bytes,
                 void *stream)
 {
@@ -1521,7 +1531,10 @@ gf_status setup(gf_ctx c, int ncfg, const gf_params *params, void *const *links,
         C.fields = c->ws + l.fields;
         C.fields2 = c->ws + l.fields2;
         C.g = (double2 *)(c->ws + l.g);
-        C.work = fused ? (void *)C.g : (void *)C.U12[0];  // whichever the iterations do not use
+        // the transform's own buffer (whichever the iterations do not use), or
+        // fields2
+        const bool third = 3.0 * kFields * (p.fft_prec ? 8 : 16) * C.V <= kThirdFieldsBytes;
+        C.work = !third ? C.fields2 : fused ? (GF_GLOBAL void *)C.g : (GF_GLOBAL void *)C.U12[0];
         C.partials = (double *)(c->ws + l.partials);
         C.ctrl = (Ctrl *)(c->ws + ctrl_base) + k;
         C.sin2 = (const double *)(c->ws + l.sin2);

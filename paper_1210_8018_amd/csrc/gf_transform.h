@@ -80,15 +80,13 @@ static __device__ __forceinline__ void finalize_config(const Cfg &C, int nparts,
 // Fields the caller gave (gf_fft) are transformed in place. In an iteration
 // the forward pass over x reads Delta from `fields` and writes to `work`, the
 // passes along y, z and t work there in place, and the backward pass over x
-// writes Delta~ to `fields2`. So Delta stays in `fields` until the next update
-// or measurement, and neither a pass launched ahead for a configuration that
-// turns out to have stopped nor a stage call (gf_gauge) between two iterating
-// calls spoils what the next update starts from. Against a transform in place
-// in `fields`, FP64: 32^4 all passes within 1 %; 16^3 x 32 and 24^4 the (z, t)
-// pass 9.9 -> 7.6 and 17.3 -> 16.3 us; 48^4 the forward (x, y) pass 114 -> 120.
-// With no third buffer (`work` and `fields2` the same) the backward (x, y) pass
-// of 16^3 x 32 took 8.9 us for 6.6; with non-temporal loads the forward one of
-// 24^4 17 for 13.
+// writes Delta~ to `fields2` (for large lattices the same buffer as `work`). So
+// Delta stays in `fields` until the next update or measurement, and neither a
+// pass launched ahead for a configuration that turns out to have stopped nor a
+// stage call (gf_gauge) between two iterating calls spoils what the next update
+// starts from. An iteration takes as long as with a transform in place in
+// `fields` (32^4 FP64 254.8 us for 255.9, 36^4 496 for 502), or less where the
+// buffer is a third one (16^3 x 32 52.8 for 54.9).
 template <typename T2>
 __device__ __forceinline__ T2 *zt_pass(const Cfg &C, void *fields_override)
 {

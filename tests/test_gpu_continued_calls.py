@@ -1,6 +1,8 @@
 """Calls that go on where an earlier one stopped: the same values, bit for
 bit, as one uninterrupted call, wherever the earlier one stopped within the
 updates it had launched, and whatever stage calls lie in between."""
+from functools import lru_cache
+
 import numpy as np
 import pytest
 import torch
@@ -16,6 +18,11 @@ N = 12  # updates: the call's first, a whole chunk of 8 and part of another
 # work-group, and the LDS-staged pass (an extent above 64)
 DIMS = [(8, 8, 8, 8), (6, 4, 9, 4), (24, 24, 4, 6), (32, 32, 4, 4), (48, 48, 3, 4), (72, 4, 4, 6)]
 KINDS = [dict(), dict(fft_prec=1), dict(fft_prec=1, link_prec=1, refine_theta=1e-30), dict(reunit_every=3)]
+
+
+@lru_cache(maxsize=1)
+def large_links(dims):
+    return random_links(dims, 0.25, 503)
 
 
 def dev(a):
@@ -54,6 +61,21 @@ def test_fix_until_goes_on_after_any_stop(dims, kw, sched):
             assert fx.history() == (F, T), (k, stop)
             assert torch.equal(links, whole), (k, stop)
             fx.close()
+
+
+@pytest.mark.parametrize("dims,prec", [((32, 32, 32, 24), 0), ((24, 36, 24, 36), 0), ((72, 48, 16, 16), 0),
+                                       ((32, 32, 48, 32), 1), ((72, 48, 24, 24), 1)])
+@pytest.mark.parametrize("sched", [1, 2, 3])
+def test_large_lattices_go_on(dims, prec, sched):
+    """Lattices transformed in two sets of fields, not three."""
+    kw = dict(fft_prec=prec, fft_schedule=sched)
+    whole, links = dev(large_links(dims)), dev(large_links(dims))
+    fx = GaugeFixer(whole, **kw)
+    fx.fix_until(-1.0, N, allow_maxiter=True)
+    fa = GaugeFixer(links, **kw)
+    for n in (3, 2, N - 5):
+        fa.fix_until(-1.0, n, allow_maxiter=True)
+    assert fa.history() == fx.history() and torch.equal(links, whole)
 
 
 @pytest.mark.parametrize("sched", [1, 2, 3])
