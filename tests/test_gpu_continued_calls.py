@@ -63,9 +63,9 @@ def test_fix_until_goes_on_after_any_stop(dims, kw, sched):
             fx.close()
 
 
+@pytest.mark.parametrize("sched", [1, 2, 3])
 @pytest.mark.parametrize("dims,prec", [((32, 32, 32, 24), 0), ((24, 36, 24, 36), 0), ((72, 48, 16, 16), 0),
                                        ((32, 32, 48, 32), 1), ((72, 48, 24, 24), 1)])
-@pytest.mark.parametrize("sched", [1, 2, 3])
 def test_large_lattices_go_on(dims, prec, sched):
     """Lattices transformed in two sets of fields, not three."""
     kw = dict(fft_prec=prec, fft_schedule=sched)
